@@ -1303,13 +1303,11 @@ struct TrainState {
     float *logp_old = nullptr, *adv = nullptr, *ret = nullptr, *vold = nullptr;
     float *mean_new = nullptr, *value_new = nullptr, *dv = nullptr;
     uint16_t *dmu = nullptr;               // [Mp of the actor's output layer][Mb], rows >= A zero
-    uint16_t *dz[2] = {nullptr, nullptr};  // [max width][Mb]
-    float *splitk = nullptr;
-    size_t splitk_floats = 0;
+    uint16_t *dz[2][2] = {};               // per network: two of [max width][Mb]
+    float *splitk[2] = {nullptr, nullptr}; // per network: split-K weight-gradient partials
     double *loss_partial = nullptr, *mb_stats = nullptr, *norm_partial = nullptr;
-    double *rowsum_part = nullptr;         // [rows][segments] of the bias-gradient sums
-    double *rs_tile = nullptr;             // [rows][column tiles]: row sums of a masked
-                                           // gradient, left by the kernel that wrote it
+    double *rs_tile[2] = {nullptr, nullptr};  // per network, [rows][column tiles]: row sums of
+                                           // a masked gradient, left by the kernel that wrote it
     double *head_part = nullptr;           // [head_K][blocks]: the critic head's weight gradient
     int norm_blocks = 0;
     float *log_std_old = nullptr;
@@ -1332,23 +1330,43 @@ namespace {
 using im::TrainLayer;
 using im::TrainState;
 
-// split-K for a weight gradient of tiles x (K = Mb): about 1024 blocks, at
-// least 4 K steps each
+// split-K for a weight gradient of `tiles` 128x128 tiles (K = Mb): about 1024
+// blocks' worth of them, at least 4 K steps each
+int64_t splitk_most(int tiles, int64_t Mb)
+{
+    return std::max<int64_t>(1, std::min<int64_t>((1024 + tiles - 1) / tiles, Mb / 256));
+}
+
 void splitk_plan(int tiles, int64_t Mb, int *splits, int *k_split)
 {
-    int64_t S = (1024 + tiles - 1) / tiles;
-    const int64_t smax = Mb / 256 > 0 ? Mb / 256 : 1;
-    if (S > smax) S = smax;
-    if (S < 1) S = 1;
-    int64_t ks = round_up((Mb + S - 1) / S, 64);
+    const int64_t S = splitk_most(tiles, Mb);
+    const int64_t ks = round_up((Mb + S - 1) / S, 64);
     *k_split = (int)ks;
     *splits = (int)((Mb + ks - 1) / ks);
 }
 
-im_status tg(bool bt, int epi, const im::TGemm &g, int splits, hipStream_t st)
+// Columns of a layer's weight-gradient GEMM: its input width padded to the
+// 256-column tile.
+int wgrad_cols(const TrainLayer &L) { return (int)round_up(L.Kp, 256); }
+int wgrad_tiles(const TrainLayer &L) { return (L.Mp / 128) * (wgrad_cols(L) / 128); }
+
+// Up to two products of one level of the actor and the critic: in one launch
+// where their tile shapes agree.
+im_status tg(bool bt, int epi, const im::TGemm *g, const int *splits, int n, hipStream_t st)
 {
-    hipError_t e = im::launch_tgemm(bt, epi, g, splits, st);
-    return e == hipSuccess ? IM_OK : hip_fail(e, "training GEMM launch");
+    im::TGemmPair p{};
+    const bool both = n == 2 && im::tgemm_bm(g[0].M) == im::tgemm_bm(g[1].M) &&
+                      im::tgemm_bn(g[0].N) == im::tgemm_bn(g[1].N);
+    for (int k = 0; k < n; k += p.n) {
+        p.n = both ? 2 : 1;
+        for (int q = 0; q < p.n; ++q) {
+            p.g[q] = g[k + q];
+            p.splits[q] = splits ? splits[k + q] : 1;
+        }
+        hipError_t e = im::launch_tgemm(bt, epi, p, st);
+        if (e != hipSuccess) return hip_fail(e, "training GEMM launch");
+    }
+    return IM_OK;
 }
 
 #define IM_CHK(call)                                          \
@@ -1369,111 +1387,140 @@ bool mbits_ok(const TrainLayer &L, int64_t Mb)
     return L.mbits && L.Mp % 256 == 0 && Mb % 256 == 0;
 }
 
-// forward of one network's GEMM layers; returns the output of the last one
-im_status net_forward(const std::vector<TrainLayer> &net, const uint16_t *x0, int Kp0, int64_t Mb,
-                      bool linear_last, float *out_last, int M_valid, hipStream_t st)
+// forward of the GEMM layers of both networks, level by level
+im_status nets_forward(im_ctx *c, TrainState *t, int64_t Mb, hipStream_t st)
 {
-    const uint16_t *x = x0;
-    int Kx = Kp0;
-    for (size_t l = 0; l < net.size(); ++l) {
-        const TrainLayer &L = net[l];
-        const bool last = linear_last && l + 1 == net.size();
-        im::TGemm g{};
-        g.A = L.wt;
-        g.lda = L.Kp;
-        g.a_bytes = (uint32_t)((uint64_t)L.Mp * L.Kp * 2);
-        g.B = x;
-        g.ldb = Mb;
-        g.b_bytes = (uint32_t)((uint64_t)Kx * Mb * 2);
-        g.M = L.Mp;
-        g.N = (int)Mb;
-        g.K = L.Kp;
-        g.k_split = L.Kp;
-        g.bias = L.bias;
-        g.ldc = Mb;
-        if (last) {
-            g.C = out_last;
-            g.M_valid = M_valid;
-            IM_CHS(tg(true, im::T_LINEAR, g, 1, st));
-        } else {
-            g.C = L.act;
-            g.mbits = mbits_ok(L, Mb) ? L.mbits : nullptr;
-            IM_CHS(tg(true, im::T_HIDDEN, g, 1, st));
+    const std::vector<TrainLayer> *nets[2] = {&t->actor, &t->critic};
+    const size_t levels = std::max(t->actor.size(), t->critic.size());
+    for (size_t l = 0; l < levels; ++l) {
+        im::TGemm hid[2];
+        int n = 0;
+        for (const auto *net : nets) {
+            if (l >= net->size()) continue;
+            const TrainLayer &L = (*net)[l];
+            im::TGemm g{};
+            g.A = L.wt;
+            g.lda = L.Kp;
+            g.a_bytes = (uint32_t)((uint64_t)L.Mp * L.Kp * 2);
+            g.B = l == 0 ? t->x0 : (*net)[l - 1].act;
+            g.ldb = Mb;
+            g.b_bytes = (uint32_t)((uint64_t)L.Kp * Mb * 2);
+            g.M = L.Mp;
+            g.N = (int)Mb;
+            g.K = L.Kp;
+            g.k_split = L.Kp;
+            g.bias = L.bias;
+            g.ldc = Mb;
+            if (net == &t->actor && l + 1 == net->size()) {
+                g.C = t->mean_new;
+                g.M_valid = c->A;
+                IM_CHS(tg(true, im::T_LINEAR, &g, nullptr, 1, st));
+            } else {
+                g.C = L.act;
+                g.mbits = mbits_ok(L, Mb) ? L.mbits : nullptr;
+                hid[n++] = g;
+            }
         }
-        x = L.act;
-        Kx = L.Mp;
+        if (n) IM_CHS(tg(true, im::T_HIDDEN, hid, nullptr, n, st));
     }
     return IM_OK;
 }
 
-// Columns of a layer's weight-gradient GEMM: its input width padded to the
-// 256-column tile.
-int wgrad_cols(const TrainLayer &L) { return (int)round_up(L.Kp, 256); }
-
-// backward of one network's GEMM layers from dz (gradient of the last GEMM
-// layer's pre-activation, [Mp][Mb] bf16): weight and bias gradients into
-// t->grad; dz buffers alternate in t->dz starting after `dz`
-im_status net_backward(TrainState *t, const std::vector<TrainLayer> &net, const uint16_t *x0,
-                       const uint16_t *dz, int64_t Mb, hipStream_t st, int top_parts = 0)
+// backward of the GEMM layers of both networks, level by level from the top,
+// from the gradients of their last GEMM layers' pre-activations ([Mp][Mb]
+// bf16: the actor's output layer t->dmu, the critic's top hidden layer
+// t->dz[1][0] with its row sums by `head_parts` column blocks in
+// t->rs_tile[1]): weight and bias gradients into t->grad (not the bias of the
+// actor's output layer, which the loss kernel sums).
+im_status nets_backward(im_ctx *c, TrainState *t, int64_t Mb, int head_parts, hipStream_t st)
 {
-    int pp = dz == t->dz[0] ? 1 : 0;
-    // dz came with its row sums in t->rs_tile, by `parts` column blocks: given
-    // for the top layer (top_parts), then left by each masked-gradient GEMM
-    bool dz_sums = top_parts > 0;
-    int parts = top_parts;
-    for (int l = (int)net.size() - 1; l >= 0; --l) {
-        const TrainLayer &L = net[l];
-        const uint16_t *X = l == 0 ? x0 : net[l - 1].act;
-        // dW = dZ^T X over the minibatch (split over it), on whole 256-column tiles:
-        // the columns past Kp read zero (outside the operand's buffer range)
-        const int Nw = wgrad_cols(L);
-        const int tiles = (L.Mp / 128) * (Nw / 128);
-        int S, ks;
-        splitk_plan(tiles, Mb, &S, &ks);
-        im::TGemm g{};
-        g.A = dz;
-        g.lda = Mb;
-        g.a_bytes = (uint32_t)((uint64_t)L.Mp * Mb * 2);
-        g.B = X;
-        g.ldb = Mb;
-        g.b_bytes = (uint32_t)((uint64_t)L.Kp * Mb * 2);
-        g.M = L.Mp;
-        g.N = Nw;
-        g.K = (int)Mb;
-        g.k_split = ks;
-        g.C = t->splitk;
-        g.ldc = Nw;
-        IM_CHS(tg(false, im::T_PARTIAL, g, S, st));
-        IM_CHK(im::launch_splitk_reduce(t->splitk, S, L.Mp, Nw, L.out, L.in, t->grad + L.w_off, st));
-        if (dz_sums)
-            IM_CHK(im::launch_rowsum_finish(t->rs_tile, L.out, parts, t->grad + L.b_off, st));
-        else
-            IM_CHK(im::launch_rowsum(true, dz, L.out, Mb, nullptr, t->rowsum_part, t->grad + L.b_off, st));
+    const std::vector<TrainLayer> *nets[2] = {&t->actor, &t->critic};
+    const uint16_t *dz[2] = {t->dmu, t->dz[1][0]};
+    int pp[2] = {0, 1};                 // the dz buffer the next gradient goes to
+    int parts[2] = {0, head_parts};     // column blocks of the row sums in rs_tile
+    for (int l = (int)std::max(t->actor.size(), t->critic.size()) - 1; l >= 0; --l) {
+        im::TGemm w[2], x[2];
+        int S[2], n = 0, who[2];
+        for (int k = 0; k < 2; ++k)
+            if (l < (int)nets[k]->size()) who[n++] = k;
+        im::ReduceArgs r{};
+        for (int q = 0; q < n; ++q) {
+            const int k = who[q];
+            const TrainLayer &L = (*nets[k])[l];
+            const uint16_t *X = l == 0 ? t->x0 : (*nets[k])[l - 1].act;
+            // dW = dZ^T X over the minibatch (split over it), on whole 256-column tiles:
+            // the columns past Kp read zero (outside the operand's buffer range)
+            const int Nw = wgrad_cols(L);
+            int ks;
+            splitk_plan(wgrad_tiles(L), Mb, &S[q], &ks);
+            im::TGemm g{};
+            g.A = dz[k];
+            g.lda = Mb;
+            g.a_bytes = (uint32_t)((uint64_t)L.Mp * Mb * 2);
+            g.B = X;
+            g.ldb = Mb;
+            g.b_bytes = (uint32_t)((uint64_t)L.Kp * Mb * 2);
+            g.M = L.Mp;
+            g.N = Nw;
+            g.K = (int)Mb;
+            g.k_split = ks;
+            g.C = t->splitk[k];
+            g.ldc = Nw;
+            w[q] = g;
+            im::ReduceJob &j = r.j[r.n++];
+            j.P = t->splitk[k];
+            j.S = S[q];
+            j.M = L.Mp;
+            j.N = Nw;
+            j.rows = L.out;
+            j.cols = L.in;
+            j.out = t->grad + L.w_off;
+            if (parts[k] > 0) {
+                j.part = t->rs_tile[k];
+                j.parts = parts[k];
+                j.prows = L.out;
+                j.row_out = t->grad + L.b_off;
+            }
+        }
+        IM_CHS(tg(false, im::T_PARTIAL, w, S, n, st));
+        if (l == (int)t->critic.size() - 1) {
+            // the critic's output layer: partials left with its top layer's gradient
+            im::ReduceJob &j = r.j[r.n++];
+            j.part = t->head_part;
+            j.parts = head_parts;
+            j.prows = t->head_K;
+            j.row_out = t->grad + t->head_w_off;
+        }
+        IM_CHK(im::launch_reduce(r, st));
         if (l == 0) break;
-        // dX^T = W^T dZ^T, masked where the layer input (a ReLU output) is 0
-        im::TGemm h{};
-        h.A = L.wtt;
-        h.lda = L.Mp;
-        h.a_bytes = (uint32_t)((uint64_t)L.Kp * L.Mp * 2);
-        h.B = dz;
-        h.ldb = Mb;
-        h.b_bytes = (uint32_t)((uint64_t)L.Mp * Mb * 2);
-        h.M = L.Kp;
-        h.N = (int)Mb;
-        h.K = L.Mp;
-        h.k_split = L.Mp;
-        h.C = t->dz[pp];
-        h.ldc = Mb;
-        h.mask = X;
-        h.ldm = Mb;
-        // the mask bits the forward of layer l - 1 wrote on the same tiles
-        if (mbits_ok(net[l - 1], Mb) && net[l - 1].Mp == L.Kp) h.mbits = net[l - 1].mbits;
-        h.rs_part = t->rs_tile;     // the bias gradient of layer l - 1, by column tile
-        IM_CHS(tg(true, im::T_MASK, h, 1, st));
-        dz_sums = true;
-        parts = (int)(Mb / im::tgemm_bn(Mb));
-        dz = t->dz[pp];
-        pp ^= 1;
+        for (int q = 0; q < n; ++q) {
+            const int k = who[q];
+            const TrainLayer &L = (*nets[k])[l], &Lb = (*nets[k])[l - 1];
+            // dX^T = W^T dZ^T, masked where the layer input (a ReLU output) is 0
+            im::TGemm h{};
+            h.A = L.wtt;
+            h.lda = L.Mp;
+            h.a_bytes = (uint32_t)((uint64_t)L.Kp * L.Mp * 2);
+            h.B = dz[k];
+            h.ldb = Mb;
+            h.b_bytes = (uint32_t)((uint64_t)L.Mp * Mb * 2);
+            h.M = L.Kp;
+            h.N = (int)Mb;
+            h.K = L.Mp;
+            h.k_split = L.Mp;
+            h.C = t->dz[k][pp[k]];
+            h.ldc = Mb;
+            h.mask = Lb.act;
+            h.ldm = Mb;
+            // the mask bits the forward of layer l - 1 wrote on the same tiles
+            if (mbits_ok(Lb, Mb) && Lb.Mp == L.Kp) h.mbits = Lb.mbits;
+            h.rs_part = t->rs_tile[k];  // the bias gradient of layer l - 1, by column tile
+            x[q] = h;
+            parts[k] = (int)(Mb / im::tgemm_bn(Mb));
+            dz[k] = t->dz[k][pp[k]];
+            pp[k] ^= 1;
+        }
+        IM_CHS(tg(true, im::T_MASK, x, nullptr, n, st));
     }
     return IM_OK;
 }
@@ -1525,8 +1572,7 @@ im_status run_minibatch(im_ctx *c, const im_ppo_batch *b, const im_ppo_params *p
     ga.vold = t->vold;
     IM_CHK(im::launch_gather(ga, st));
     // forward
-    IM_CHS(net_forward(t->actor, t->x0, t->Kp0, Mbp, true, t->mean_new, c->A, st));
-    IM_CHS(net_forward(t->critic, t->x0, t->Kp0, Mbp, false, nullptr, 0, st));
+    IM_CHS(nets_forward(c, t, Mbp, st));
     const TrainLayer &hl = t->critic.back();
     const float *head = c->critic.d_head;
     IM_CHK(im::launch_head_forward(hl.act, t->head_K, Mbp, head, head + c->critic.K_head, t->value_new,
@@ -1557,33 +1603,39 @@ im_status run_minibatch(im_ctx *c, const im_ppo_batch *b, const im_ppo_params *p
     IM_CHK(im::launch_loss(la, st));
     im::LossReduceArgs lr{};
     lr.partial = t->loss_partial;
-    lr.blocks = (int)(Mbp / 256);
+    lr.blocks = (int)(Mbp / im::LOSS_BLOCK);
     lr.A = c->A;
     lr.Mb = Mb;
     lr.entropy_coef = p->entropy_coef;
     lr.grad_log_std = t->grad + t->log_std_off;
+    lr.grad_bias = t->grad + t->actor.back().b_off;
+    lr.grad_vbias = t->grad + t->head_b_off;
     lr.mb_stats = t->mb_stats;
     IM_CHK(im::launch_loss_reduce(lr, st));
-    // backward: actor from the output-layer gradient, critic from dV
-    IM_CHS(net_backward(t, t->actor, t->x0, t->dmu, Mbp, st));
-    IM_CHK(im::launch_rowsum(false, t->dv, 1, Mbp, nullptr, t->rowsum_part, t->grad + t->head_b_off, st));
-    // the head's weight gradient and the top hidden layer's bias-gradient sums
+    // backward: actor from the output-layer gradient, critic from dV; the
+    // head's weight gradient and the top hidden layer's bias-gradient sums
     // come out of the kernel that forms that layer's gradient
     const int hparts = (int)((Mbp / 8 + 255) / 256);
-    IM_CHK(im::launch_head_backward(hl.act, t->head_K, hl.Mp, Mbp, head, t->dv, t->dz[0], t->head_part,
-                                    t->rs_tile, st));
-    IM_CHK(im::launch_rowsum_finish(t->head_part, t->head_K, hparts, t->grad + t->head_w_off, st));
-    IM_CHS(net_backward(t, t->critic, t->x0, t->dz[0], Mbp, st, hparts));
-    return IM_OK;
+    IM_CHK(im::launch_head_backward(hl.act, t->head_K, hl.Mp, Mbp, head, t->dv, t->dz[1][0], t->head_part,
+                                    t->rs_tile[1], st));
+    return nets_backward(c, t, Mbp, hparts, st);
 }
 
 // training and rollout copies of every layer from the masters
 im_status repack_all(im_ctx *c, hipStream_t st)
 {
     TrainState *t = c->train;
+    im::RepackMulti p{};
+    auto flush = [&]() {
+        const hipError_t e = p.n ? im::launch_repack(p, st) : hipSuccess;
+        p.n = 0;
+        return e;
+    };
+    auto next = [&]() -> im::RepackArgs & { return p.r[p.n++] = im::RepackArgs{}; };
     for (auto *net : {&t->actor, &t->critic})
         for (const TrainLayer &L : *net) {
-            im::RepackArgs r{};
+            if (p.n == im::MAX_REPACK) IM_CHK(flush());
+            im::RepackArgs &r = next();
             r.W = t->x + L.w_off;
             r.b = t->x + L.b_off;
             r.out = L.out;
@@ -1598,10 +1650,10 @@ im_status repack_all(im_ctx *c, hipStream_t st)
             r.roll_bf16 = 1;
             r.bias_train = L.bias;
             r.bias_roll = L.roll_bias;
-            IM_CHK(im::launch_repack(r, st));
         }
+    if (p.n + 2 > im::MAX_REPACK) IM_CHK(flush());
     // the critic's output layer (bf16-rounded weights, as the forward uses them)
-    im::RepackArgs h{};
+    im::RepackArgs &h = next();
     h.W = t->x + t->head_w_off;
     h.b = t->x + t->head_b_off;
     h.out = 1;
@@ -1610,9 +1662,14 @@ im_status repack_all(im_ctx *c, hipStream_t st)
     h.roll_K = 0;
     h.roll_bf16 = 2;
     h.bias_roll = c->critic.d_head + c->critic.K_head;
-    IM_CHK(im::launch_repack(h, st));
-    IM_CHK(hipMemcpyAsync(c->d_log_std, t->x + t->log_std_off, sizeof(float) * c->A,
-                          hipMemcpyDeviceToDevice, st));
+    // log sigma, as it is
+    im::RepackArgs &ls = next();
+    ls.W = t->x + t->log_std_off;
+    ls.out = c->A;
+    ls.in = 1;
+    ls.roll = c->d_log_std;
+    ls.roll_K = 1;
+    IM_CHK(flush());
     return IM_OK;
 }
 
@@ -1723,7 +1780,7 @@ im_status im_ppo_setup(im_ctx *c, int64_t max_minibatch)
     if (!alloc(&t->x, 4 * P) || !alloc(&t->m, 4 * P) || !alloc(&t->v, 4 * P) || !alloc(&t->grad, 4 * P) ||
         !alloc(&t->step, sizeof(int)) || !alloc(&t->opt, sizeof(im::OptScalars)))
         return oom();
-    size_t sk = 0;
+    size_t sk[2] = {0, 0};
     for (auto *net : {&t->actor, &t->critic}) {
         for (size_t l = 0; l < net->size(); ++l) {
             TrainLayer &L = (*net)[l];
@@ -1733,9 +1790,10 @@ im_status im_ppo_setup(im_ctx *c, int64_t max_minibatch)
                 return oom();
             if (!out_layer && !alloc(&L.act, (size_t)L.Mp * Mb * 2)) return oom();
             if (!out_layer && L.Mp % 256 == 0 && !alloc(&L.mbits, (size_t)L.Mp * Mb / 8)) return oom();
-            int S, ks;
-            splitk_plan((L.Mp / 128) * (wgrad_cols(L) / 128), Mb, &S, &ks);
-            sk = std::max(sk, (size_t)S * L.Mp * wgrad_cols(L));
+            // a smaller minibatch has no more splits
+            const int64_t S = splitk_most(wgrad_tiles(L), Mb);
+            size_t &most = sk[net == &t->critic];
+            most = std::max(most, (size_t)S * L.Mp * wgrad_cols(L));
         }
     }
     const int A = c->A;
@@ -1745,17 +1803,16 @@ im_status im_ppo_setup(im_ctx *c, int64_t max_minibatch)
         !alloc(&t->adv, 4 * (size_t)Mb) || !alloc(&t->ret, 4 * (size_t)Mb) || !alloc(&t->vold, 4 * (size_t)Mb) ||
         !alloc(&t->mean_new, 4 * (size_t)A * Mb) || !alloc(&t->value_new, 4 * (size_t)Mb) ||
         !alloc(&t->dv, 4 * (size_t)Mb) || !alloc(&t->dmu, (size_t)al.Mp * Mb * 2) ||
-        !alloc(&t->dz[0], (size_t)maxw * Mb * 2) || !alloc(&t->dz[1], (size_t)maxw * Mb * 2) ||
-        !alloc(&t->splitk, 4 * sk) ||
-        !alloc(&t->loss_partial, sizeof(double) * (size_t)(Mb / 256) * (A + im::LOSS_STATS)) ||
+        !alloc(&t->dz[0][0], (size_t)maxw * Mb * 2) || !alloc(&t->dz[0][1], (size_t)maxw * Mb * 2) ||
+        !alloc(&t->dz[1][0], (size_t)maxw * Mb * 2) || !alloc(&t->dz[1][1], (size_t)maxw * Mb * 2) ||
+        !alloc(&t->splitk[0], 4 * sk[0]) || !alloc(&t->splitk[1], 4 * sk[1]) ||
+        !alloc(&t->loss_partial, sizeof(double) * (size_t)(Mb / im::LOSS_BLOCK) * im::loss_fields(A)) ||
         !alloc(&t->mb_stats, sizeof(double) * im::LOSS_STATS) || !alloc(&t->log_std_old, 4 * (size_t)A))
         return oom();
-    t->splitk_floats = sk;
     t->norm_blocks = (int)std::min<int64_t>(1024, (t->P + 255) / 256);
     if (!alloc(&t->norm_partial, sizeof(double) * t->norm_blocks)) return oom();
-    // row sums: rows x segments <= 2048 + rows for any row count
-    if (!alloc(&t->rowsum_part, sizeof(double) * (2048 + (size_t)maxw + 1))) return oom();
-    if (!alloc(&t->rs_tile, sizeof(double) * (size_t)maxw * (size_t)(Mb / 128 + 1))) return oom();
+    for (double *&rs : t->rs_tile)
+        if (!alloc(&rs, sizeof(double) * (size_t)maxw * (size_t)(Mb / 128 + 1))) return oom();
     if (!alloc(&t->head_part, sizeof(double) * (size_t)maxw * (size_t)(Mb / 2048 + 1))) return oom();
     // the rollout copies the update refreshes
     for (size_t l = 0; l < t->actor.size(); ++l) {

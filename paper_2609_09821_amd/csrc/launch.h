@@ -133,7 +133,17 @@ struct TGemm {
                          // reads them instead of `mask` (the bits its M x N producer wrote)
 };
 
-// Column tile width of the training GEMM for N columns.
+// One or two products on the same tile shape and epilogue in one launch (the
+// actor's and the critic's layer): g[1] unused when n == 1.
+struct TGemmPair {
+    TGemm g[2];
+    int n;
+    int splits[2];       // K splits of each (PARTIAL; else 1)
+    int blocks0;         // blocks of g[0] (set by the launcher)
+};
+
+// Tile of the training GEMM: rows for M rows, columns for N columns.
+inline int tgemm_bm(int64_t M) { return M % 256 == 0 ? 256 : 128; }
 inline int tgemm_bn(int64_t N) { return N % 256 == 0 ? 256 : 128; }
 
 struct GatherArgs {
@@ -165,8 +175,14 @@ struct LossArgs {
     int clipped_value_loss;
     uint16_t *dmu;                  // [A][Mb_pad] bf16 out
     float *dv;                      // [Mb_pad] out
-    double *partial;                // [blocks][A + LOSS_STATS]
+    double *partial;                // [loss_fields(A)][Mb_pad / LOSS_BLOCK]
 };
+
+// Samples per block of the loss kernel and fields of its partials: the
+// log-std gradient (A), the output layer's bias gradient (A: the sums of the
+// stored bf16 gradient of the mean), the value's gradient (1), the stats.
+constexpr int LOSS_BLOCK = 256;
+constexpr int loss_fields(int A) { return 2 * A + 1 + LOSS_STATS; }
 
 struct LossReduceArgs {
     const double *partial;
@@ -174,7 +190,29 @@ struct LossReduceArgs {
     int64_t Mb;
     float entropy_coef;
     float *grad_log_std;   // [A]
+    float *grad_bias;      // [A] bias of the actor's output layer
+    float *grad_vbias;     // [1] bias of the critic's output layer
     double *mb_stats;      // [LOSS_STATS] minibatch means
+};
+
+// Sums of split partials into the flat gradient, up to MAX_REDUCE per launch:
+// out[o][i] = sum_z P[z][o][i] (fp32, P [S][M][N], o < rows, i < cols) and
+// row_out[r] = sum_k part[r * parts + k] (float64, r < prows).  Either part
+// may be empty (rows == 0, prows == 0).
+struct ReduceJob {
+    const float *P;
+    int S, M, N, rows, cols;
+    float *out;
+    const double *part;
+    int parts, prows;
+    float *row_out;
+};
+constexpr int MAX_REDUCE = 3;
+struct ReduceArgs {
+    ReduceJob j[MAX_REDUCE];
+    int n;
+    int end[2 * MAX_REDUCE];   // first block past each job's weight and row blocks (set by
+                               // the launcher)
 };
 
 struct OptScalars {
@@ -205,7 +243,16 @@ struct RepackArgs {
     float *bias_train, *bias_roll;
 };
 
-hipError_t launch_tgemm(bool bt, int epi, const TGemm &g, int splits, hipStream_t s);
+// Weight refreshes of several layers in one launch.
+constexpr int MAX_REPACK = 12;
+struct RepackMulti {
+    RepackArgs r[MAX_REPACK];
+    int n;
+    int end[MAX_REPACK];       // first block past each layer's (set by the launcher)
+};
+
+// The products of p must share the tile shape (tgemm_bm of M, tgemm_bn of N).
+hipError_t launch_tgemm(bool bt, int epi, TGemmPair p, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 hipError_t launch_head_forward(const uint16_t *h, int K, int64_t Mb, const float *w, const float *b,
                                float *v, hipStream_t s);
@@ -213,20 +260,12 @@ hipError_t launch_head_forward(const uint16_t *h, int K, int64_t Mb, const float
 // gradient and of the rows' sums of the stored dz.
 hipError_t launch_head_backward(const uint16_t *h, int K, int rows, int64_t Mb, const float *w,
                                 const float *dv, uint16_t *dz, double *pw, double *pb, hipStream_t s);
-// part: [rows][up to 2048 / rows + 1] float64 scratch
-hipError_t launch_rowsum(bool bf16, const void *x, int rows, int64_t Mb, const float *y, double *part,
-                         float *out, hipStream_t s);
-// out[r] = sum over k < parts of part[r * parts + k] (float64, k in order), r < rows.
-hipError_t launch_rowsum_finish(const double *part, int rows, int parts, float *out, hipStream_t s);
-hipError_t launch_splitk_reduce(const float *P, int S, int64_t M, int64_t N, int rows, int cols,
-                                float *out, hipStream_t s);
+hipError_t launch_reduce(ReduceArgs r, hipStream_t s);
 hipError_t launch_loss(const LossArgs &a, hipStream_t s);
 hipError_t launch_loss_reduce(const LossReduceArgs &r, hipStream_t s);
 hipError_t launch_optimizer(const float *grad, int64_t P, double *norm_partial, int norm_blocks,
                             const FinalizeArgs &f, float *x, float *m, float *v, hipStream_t s);
-hipError_t launch_norm(const float *grad, int64_t P, double *norm_partial, int norm_blocks,
-                       hipStream_t s);
-hipError_t launch_repack(const RepackArgs &r, hipStream_t s);
+hipError_t launch_repack(RepackMulti r, hipStream_t s);
 
 hipError_t launch_env_step(int n_slots, int walk_slots, const EnvArgs &a, hipStream_t s);
 hipError_t launch_reset(int n_slots, const EnvArgs &a, hipStream_t s);

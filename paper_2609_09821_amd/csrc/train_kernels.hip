@@ -55,6 +55,37 @@ __device__ __forceinline__ float lane_group_sum(float x)
     return x;
 }
 
+// The same over a wavefront in float64, returned in lane 63: the row sums,
+// then row 0 into row 1 and row 2 into row 3 (row broadcast of lane 15), then
+// rows 0-1 into rows 2-3 (row broadcast of lane 31).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double x)
+{
+    const int2 v = __builtin_bit_cast(int2, x);
+    int2 t;
+    t.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, ROW_MASK, 0xF, true);
+    t.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, ROW_MASK, 0xF, true);
+    return x + __builtin_bit_cast(double, t);
+}
+
+__device__ __forceinline__ double wave_sum63(double x)
+{
+    x = dpp_add<0x111, 0xF>(x);
+    x = dpp_add<0x112, 0xF>(x);
+    x = dpp_add<0x114, 0xF>(x);
+    x = dpp_add<0x118, 0xF>(x);
+    x = dpp_add<0x142, 0xA>(x);
+    return dpp_add<0x143, 0xC>(x);
+}
+
+// Block b of n -> position in an order where the blocks of one XCD (b mod 8)
+// are consecutive.
+__device__ __forceinline__ int xcd_order(int b, int n)
+{
+    const int x = b & 7, per = n >> 3, rem = n & 7;
+    return x * per + (x < rem ? x : rem) + (b >> 3);
+}
+
 // ---------------------------------------------------------------------------
 // GEMM: tiles of BM = 64 WM rows by BN columns (WM x 2 waves, each wave
 // 64 x BN/2 = 2 x BN/64 MFMA 32x32x16 tiles).  launch_tgemm picks WM = 4
@@ -69,12 +100,19 @@ __device__ __forceinline__ float lane_group_sum(float x)
 // group, lane 4j+q addresses row k0+j, columns n0+4q..n0+4q+3, and lane l
 // receives rows k0..k0+3 of column n0+l (two reads give the 8 consecutive k
 // of a bf16 fragment; the 32-byte row shift of the padding keeps a group's
-// four rows on distinct banks).  blockIdx.y splits K (weight gradients: K =
-// the minibatch).  All operands are zero-padded to whole tiles.
+// four rows on distinct banks).  A split K (weight gradients: K = the
+// minibatch) takes one block per tile and split.  All operands are zero-padded to whole tiles.
 // ---------------------------------------------------------------------------
 template <bool BT, int EPI, int WM, int BN>
-__global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
+__global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
 {
+    // this block's product, tile and K split: blocks of one XCD (dispatched
+    // round robin over the 8) take consecutive (split, tile) numbers, so that
+    // the tiles that share a B panel (or, split, a K range) share an L2
+    int id = xcd_order(blockIdx.x, gridDim.x);
+    const bool second = id >= p.blocks0;
+    if (second) id -= p.blocks0;
+    const TGemm g = second ? p.g[1] : p.g[0];
     // WM x 2 waves, each 64 x BN/2 (TN = BN/64 MFMA tiles across); tile BM x BN
     constexpr int NT = 128 * WM;
     constexpr int TN = BN / 64;
@@ -87,9 +125,11 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;   // wave: 64 x 64 of the tile
     const int mblocks = g.M / BM;
-    const int64_t m0 = (int64_t)(blockIdx.x % mblocks) * BM;
-    const int64_t n0 = (int64_t)(blockIdx.x / mblocks) * BN;
-    const int kb = blockIdx.y * g.k_split;
+    const int tiles = mblocks * (g.N / BN);
+    const int tile = id % tiles, split = id / tiles;
+    const int64_t m0 = (int64_t)(tile % mblocks) * BM;
+    const int64_t n0 = (int64_t)(tile / mblocks) * BN;
+    const int kb = split * g.k_split;
     const int ke = kb + g.k_split < g.K ? kb + g.k_split : g.K;
     const int nk = (ke - kb) / BK;
     // mask bits (256x256 tiles): the 16 pieces this thread writes in the
@@ -97,7 +137,7 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
     constexpr bool MBITS = BM == 256 && BN == 256 && (EPI == T_HIDDEN || EPI == T_MASK);
     uint4 mbits_in = make_uint4(0u, 0u, 0u, 0u);
     if constexpr (MBITS && EPI == T_MASK)
-        if (g.mbits) mbits_in = g.mbits[(int64_t)blockIdx.x * NT + tid];
+        if (g.mbits) mbits_in = g.mbits[(int64_t)tile * NT + tid];
 
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
         (void *)g.A, (short)0, (int)g.a_bytes, 0x00020000);
@@ -286,7 +326,7 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
         }
         if constexpr (MBITS && EPI == T_HIDDEN)
             if (g.mbits)
-                g.mbits[(int64_t)blockIdx.x * NT + tid] =
+                g.mbits[(int64_t)tile * NT + tid] =
                     make_uint4(mbits_out[0], mbits_out[1], mbits_out[2], mbits_out[3]);
     } else {
 #pragma unroll
@@ -303,7 +343,7 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
                         if constexpr (EPI == T_LINEAR) {
                             if (m < g.M_valid) ((float *)g.C)[m * g.ldc + n] = v + g.bias[m];
                         } else {
-                            ((float *)g.C)[((int64_t)blockIdx.y * g.M + m) * g.ldc + n] = v;
+                            ((float *)g.C)[((int64_t)split * g.M + m) * g.ldc + n] = v;
                         }
                     }
             }
@@ -313,16 +353,21 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemm g)
 // ---------------------------------------------------------------------------
 // Minibatch gather.  Column j = 64 c + l of the minibatch is env e0 + l of
 // step t, where chunk c of the minibatch is q = perm[c]: t = q / (N/64),
-// e0 = 64 (q % (N/64)).  One wavefront per chunk; chunks past the
-// minibatch's end write zeros (padding columns).  The chunk's actions and
-// means ([64][A] floats, contiguous in the [T][N][A] storage) are read 32
-// columns at a time with loads of whole 128-byte row pieces into the wave's
-// LDS slice (rows of 33 floats: the transposed reads hit 64 distinct banks)
-// and written out as [A][Mb] rows of 64 samples.
+// e0 = 64 (q % (N/64)).  One wavefront per chunk and part (blockIdx.y): parts
+// of GATHER_ROWS observation rows, then parts of GATHER_COLS columns of the
+// actions and of the means; chunks past the minibatch's end write zeros
+// (padding columns).  One wavefront per chunk for everything left a small
+// minibatch on 512 wavefronts (32768 samples of 226 rows: 38 us; by parts
+// 17 us).  The chunk's actions and means ([64][A] floats, contiguous
+// in the [T][N][A] storage) are read with loads of whole 128-byte row pieces
+// into the wave's LDS slice (rows of 33 floats: the transposed reads hit 64
+// distinct banks) and written out as [A][Mb] rows of 64 samples.
 // ---------------------------------------------------------------------------
+constexpr int GATHER_ROWS = 64, GATHER_COLS = 32;
+
 __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 {
-    constexpr int KC = 32, LDC = KC + 1;
+    constexpr int KC = GATHER_COLS, LDC = KC + 1;
     __shared__ float gather_lds[4][64 * LDC];
     const int lane = threadIdx.x & 63;
     const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -330,85 +375,101 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
     if (c >= a.chunks_pad) return;
     const int64_t j = (int64_t)c * 64 + lane;
     const int64_t Mb = a.Mb_pad;
-    if (c >= a.chunks) {
-        for (int i = 0; i < a.K0; ++i) a.x0[i * Mb + j] = 0;
-        for (int k = 0; k < a.A; ++k) {
-            a.act[k * Mb + j] = 0.0f;
-            a.mean_old[k * Mb + j] = 0.0f;
-        }
-        a.logp_old[j] = 0.0f;
-        a.adv[j] = 0.0f;
-        a.ret[j] = 0.0f;
-        a.vold[j] = 0.0f;
-        return;
-    }
-    int q = a.perm[c];
+    const bool pad = c >= a.chunks;
+    int q = pad ? 0 : a.perm[c];
     q = q < 0 ? 0 : (q >= a.n_chunks ? a.n_chunks - 1 : q);   // memory safety only
     const int64_t t = q / a.cpt;
     const int64_t e = (int64_t)(q % a.cpt) * 64 + lane;
-    const float *o = a.obs + t * a.D * a.ld + e;
-    int i = 0;
-    for (; i + 8 <= a.D; i += 8) {
-        float v[8];
+    const int obs_parts = (a.K0 + GATHER_ROWS - 1) / GATHER_ROWS;
+    int part = blockIdx.y;
+    if (part < obs_parts) {
+        int i = part * GATHER_ROWS;
+        const int end = i + GATHER_ROWS < a.K0 ? i + GATHER_ROWS : a.K0;
+        const int live = pad ? i : (end < a.D ? end : a.D);
+        const float *o = a.obs + t * a.D * a.ld + e;
+        for (; i + 16 <= live; i += 16) {
+            float v[16];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = o[(int64_t)(i + k) * a.ld];
+            for (int k = 0; k < 16; ++k) v[k] = o[(int64_t)(i + k) * a.ld];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a.x0[(i + k) * Mb + j] = f32_to_bf16_rne(v[k]);
-    }
-    for (; i < a.D; ++i) a.x0[i * Mb + j] = f32_to_bf16_rne(o[(int64_t)i * a.ld]);
-    for (; i < a.K0; ++i) a.x0[i * Mb + j] = 0;
-    const int64_t blk = (t * a.N + (e - lane)) * a.A;   // the chunk's [64][A] block
-#pragma unroll 1
-    for (int arr = 0; arr < 2; ++arr) {
-        const float *src = (arr == 0 ? a.action : a.mean) + blk;
-        float *dst = arr == 0 ? a.act : a.mean_old;
-        for (int k0 = 0; k0 < a.A; k0 += KC) {
-            const int kc = a.A - k0 < KC ? a.A - k0 : KC;
-            // the LDS slice is the wave's own and a wave's LDS operations complete
-            // in order: no barrier between these writes and the reads below
-#pragma unroll 4
-            for (int x = lane; x < 64 * KC; x += 64) {
-                const int r = x / KC, cc = x % KC;
-                if (cc < kc) sh[r * LDC + cc] = src[(int64_t)r * a.A + k0 + cc];
-            }
-            for (int cc = 0; cc < kc; ++cc) dst[(int64_t)(k0 + cc) * Mb + j] = sh[lane * LDC + cc];
+            for (int k = 0; k < 16; ++k) a.x0[(i + k) * Mb + j] = f32_to_bf16_rne(v[k]);
         }
+        for (; i < live; ++i) a.x0[i * Mb + j] = f32_to_bf16_rne(o[(int64_t)i * a.ld]);
+        for (; i < end; ++i) a.x0[i * Mb + j] = 0;
+        if (part == 0) {
+            const int64_t s = t * a.ld + e;
+            a.logp_old[j] = pad ? 0.0f : a.logp[s];
+            a.adv[j] = pad ? 0.0f : a.adv_src[s];
+            a.ret[j] = pad ? 0.0f : a.ret_src[s];
+            a.vold[j] = pad ? 0.0f : a.value[s];
+        }
+        return;
     }
-    const int64_t s = t * a.ld + e;
-    a.logp_old[j] = a.logp[s];
-    a.adv[j] = a.adv_src[s];
-    a.ret[j] = a.ret_src[s];
-    a.vold[j] = a.value[s];
+    part -= obs_parts;
+    const int col_parts = (a.A + KC - 1) / KC;
+    const bool means = part >= col_parts;
+    const int k0 = (means ? part - col_parts : part) * KC;
+    const int kc = a.A - k0 < KC ? a.A - k0 : KC;
+    float *dst = (means ? a.mean_old : a.act) + k0 * Mb + j;
+    if (pad) {
+        for (int cc = 0; cc < kc; ++cc) dst[cc * Mb] = 0.0f;
+        return;
+    }
+    const float *src = (means ? a.mean : a.action) + (t * a.N + (e - lane)) * a.A + k0;
+    // the LDS slice is the wave's own and a wave's LDS operations complete
+    // in order: no barrier between these writes and the reads below
+#pragma unroll 16
+    for (int x = lane; x < 64 * KC; x += 64) {
+        const int r = x / KC, cc = x % KC;
+        if (cc < kc) sh[r * LDC + cc] = src[(int64_t)r * a.A + cc];
+    }
+    for (int cc = 0; cc < kc; ++cc) dst[cc * Mb] = sh[lane * LDC + cc];
 }
 
 // ---------------------------------------------------------------------------
 // Critic head (width-1 output layer) on feature-major activations.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void head_forward_kernel(const uint16_t *__restrict__ h, int K,
-                                                           int64_t Mb, const float *__restrict__ w,
-                                                           const float *__restrict__ b,
-                                                           float *__restrict__ v)
+// Two samples per thread, a wavefront per block, each sample's sum over the
+// rows in order; rows in chunks of 32, two chunk buffers in turn so that 32 to
+// 64 loads are in flight (rows past the last load the last).  Eight samples
+// per thread with 4 loads in flight left 32768 samples on 16 blocks (50 us;
+// 524288 samples 112 us; now 24 and 125 us).
+__global__ __launch_bounds__(64) void head_forward_kernel(const uint16_t *__restrict__ h, int K,
+                                                          int64_t Mb, const float *__restrict__ w,
+                                                          const float *__restrict__ b,
+                                                          float *__restrict__ v)
 {
-    // 8 consecutive samples per thread (16-byte loads); each sample's sum runs
-    // over k in order, as one sample per thread would
-    const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
-    if (j >= Mb) return;
-    float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-    for (int k = 0; k < K; ++k) {
-        const uint4 x = *(const uint4 *)(h + k * Mb + j);
-        const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
-        const float wk = w[k];
+    constexpr int C = 32;
+    const int64_t j = ((int64_t)blockIdx.x * 64 + threadIdx.x) * 2;
+    uint32_t xa[C], xb[C];
+    float wa, wb;      // the chunk's weights, one per lane
+    auto load = [&](int k0, uint32_t (&x)[C], float &wl) {
+        const int kw = k0 + (threadIdx.x & (C - 1));
+        wl = w[kw < K ? kw : K - 1];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            acc[2 * q] += wk * bf16_to_f32((uint16_t)(xw[q] & 0xFFFFu));
-            acc[2 * q + 1] += wk * bf16_to_f32((uint16_t)(xw[q] >> 16));
+        for (int i = 0; i < C; ++i) {
+            const int k = k0 + i < K ? k0 + i : K - 1;
+            x[i] = *(const uint32_t *)(h + k * Mb + j);
         }
+    };
+    float s0 = 0.0f, s1 = 0.0f;
+    auto sum = [&](int k0, const uint32_t (&x)[C], float wl) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (k0 + i >= K) break;
+            const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), i));
+            s0 += wk * __uint_as_float(x[i] << 16);
+            s1 += wk * __uint_as_float(x[i] & 0xFFFF0000u);
+        }
+    };
+    load(0, xa, wa);
+    for (int k0 = 0; k0 < K; k0 += 2 * C) {
+        load(k0 + C, xb, wb);
+        sum(k0, xa, wa);
+        load(k0 + 2 * C, xa, wa);
+        if (k0 + C < K) sum(k0 + C, xb, wb);
     }
-    const float4 o0 = make_float4(acc[0] + b[0], acc[1] + b[0], acc[2] + b[0], acc[3] + b[0]);
-    const float4 o1 = make_float4(acc[4] + b[0], acc[5] + b[0], acc[6] + b[0], acc[7] + b[0]);
-    *(float4 *)(v + j) = o0;
-    *(float4 *)(v + j + 4) = o1;
+    *(float2 *)(v + j) = make_float2(s0 + b[0], s1 + b[0]);
 }
 
 // dZ^T[k][j] = w[k] dV[j] where h[k][j] > 0 (bf16), for the last hidden
@@ -475,124 +536,117 @@ __global__ __launch_bounds__(256) void head_backward_kernel(const uint16_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// Per-row sums over the minibatch, float64 in a fixed order:
-// out[r] = sum_j x[r][j] (x bf16 or fp32), optionally times y[j].  Each row
-// is cut into `parts` segments (blockIdx.y), read in 16-byte pieces; the
-// segment sums are added in segment order by rowsum_finish_kernel.
+// Sums of split partials (ReduceArgs): a weight block takes 256 outputs, one
+// per thread, their splits added in order, 32 loads in flight at a time (one
+// after the other, the 256 splits of a 28 x 512 layer took 31 us); a row
+// block takes 4 rows, one per wavefront, the lanes every 64th partial, a
+// fixed pattern over the lanes.  Bound by the partials' bytes
+// (67 MB of 32 splits of two 512 x 1024 layers: 24 us).
 // ---------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(256) void rowsum_kernel(const void *__restrict__ x, int64_t Mb,
-                                                     const float *__restrict__ y, int parts,
-                                                     double *__restrict__ part)
+__global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs r)
 {
-    __shared__ double red[256];
-    constexpr int E = BF16 ? 8 : 4;             // elements per 16-byte piece
-    const int r = blockIdx.x, seg = blockIdx.y;
-    const int64_t len = Mb / parts;             // Mb and len are multiples of 256
-    const int64_t j0 = seg * len;
-    double s = 0.0;
-    for (int64_t j = j0 + (int64_t)threadIdx.x * E; j < j0 + len; j += 256 * E) {
-        float v[E];
-        if constexpr (BF16) {
-            const uint4 q = *(const uint4 *)((const uint16_t *)x + r * Mb + j);
-            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    constexpr int ZC = 32;
+    int job = 0;
+    bool rows = false;
+    int b = blockIdx.x;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[2 * k] = bf16_to_f32((uint16_t)(w[k] & 0xFFFF));
-                v[2 * k + 1] = bf16_to_f32((uint16_t)(w[k] >> 16));
-            }
-        } else {
-            const float4 q = *(const float4 *)((const float *)x + r * Mb + j);
-            v[0] = q.x;
-            v[1] = q.y;
-            v[2] = q.z;
-            v[3] = q.w;
+    for (int k = 2 * MAX_REDUCE - 1; k >= 0; --k)
+        if (k < 2 * r.n && (int)blockIdx.x < r.end[k]) {
+            job = k >> 1;
+            rows = k & 1;
+            b = (int)blockIdx.x - (k > 0 ? r.end[k - 1] : 0);
         }
-        if (y) {
-#pragma unroll
-            for (int k = 0; k < E; ++k) s += (double)v[k] * (double)y[j + k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) s += (double)v[k];
-        }
+    const ReduceJob g = job == 0 ? r.j[0] : (job == 1 ? r.j[1] : r.j[2]);
+    const int tid = threadIdx.x;
+    if (rows) {
+        const int row = b * 4 + (tid >> 6), lane = tid & 63;
+        if (row >= g.prows) return;
+        double s = 0.0;
+        for (int k = lane; k < g.parts; k += 64) s += g.part[(int64_t)row * g.parts + k];
+        s = wave_sum63(s);
+        if (lane == 63) g.row_out[row] = (float)s;
+        return;
     }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(int64_t)r * parts + seg] = red[0];
-}
-
-// One block per row: thread i adds parts i, i + 256, ... in order, then a
-// fixed tree over the block.
-__global__ __launch_bounds__(256) void rowsum_finish_rows_kernel(const double *__restrict__ part,
-                                                                 int parts, float *__restrict__ out)
-{
-    __shared__ double red[256];
-    const int r = blockIdx.x;
-    double s = 0.0;
-    for (int k = threadIdx.x; k < parts; k += 256) s += part[(int64_t)r * parts + k];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[r] = (float)red[0];
-}
-
-__global__ __launch_bounds__(256) void rowsum_finish_kernel(const double *__restrict__ part, int rows,
-                                                            int parts, float *__restrict__ out)
-{
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= rows) return;
-    double s = 0.0;
-    for (int k = 0; k < parts; ++k) s += part[(int64_t)r * parts + k];
-    out[r] = (float)s;
-}
-
-// Weight gradient from the split-K partials: out[o][i] = sum_z P[z][o][i]
-// (z in order) for o < rows, i < cols.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ P, int S,
-                                                            int64_t M, int64_t N, int rows,
-                                                            int cols, float *__restrict__ out)
-{
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)rows * cols) return;
-    const int64_t o = idx / cols, i = idx % cols;
+    const int idx = b * 256 + tid;
+    if (idx >= g.rows * g.cols) return;
+    const float *p = g.P + (int64_t)(idx / g.cols) * g.N + idx % g.cols;
+    const int64_t stride = (int64_t)g.M * g.N;
     float s = 0.0f;
-    for (int z = 0; z < S; ++z) s += P[((int64_t)z * M + o) * N + i];
-    out[idx] = s;
+    int z = 0;
+    for (; z + ZC <= g.S; z += ZC) {
+        float x[ZC];
+#pragma unroll
+        for (int i = 0; i < ZC; ++i) x[i] = p[(z + i) * stride];
+#pragma unroll
+        for (int i = 0; i < ZC; ++i) s += x[i];
+    }
+#pragma unroll 8
+    for (; z < g.S; ++z) s += p[z * stride];
+    g.out[idx] = s;
 }
 
 // ---------------------------------------------------------------------------
 // Loss: per sample, the clipped surrogate, value loss and KL; writes the
 // bf16 output-layer gradient dmu^T [A][Mb] (zero for padding columns), dV,
-// and per-block float64 partials: the log-std gradient (A) then the stats.
+// and per-block float64 partials of the loss fields, field-major.  A block
+// takes 256 samples with four threads each, which split the actions (256
+// consecutive threads read a 1 KB row piece): the terms of the
+// log-likelihood and the KL pass through LDS by chunks of 16 actions, where
+// one thread per sample each adds them in action order; then every wave sums
+// its actions' partials over its lanes by a fixed pattern, the block's four
+// waves of an action in order.  One thread per sample over all actions left
+// 32768 samples on 128 blocks of 4 waves (28 actions: 43 us; 524288 samples
+// of 69 actions 216 us; now 17 and 204 us).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void loss_kernel(LossArgs a)
+__global__ __launch_bounds__(1024) void loss_kernel(LossArgs a)
 {
-    __shared__ double red[4][MAX_ACTIONS + LOSS_STATS];
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int KC = 16;
+    __shared__ float sh_logp[2][KC][LOSS_BLOCK], sh_kl[2][KC][LOSS_BLOCK];
+    __shared__ float sum_logp[LOSS_BLOCK];
+    __shared__ double red[4][loss_fields(MAX_ACTIONS)];
+    const int lane = threadIdx.x & 63, sj = threadIdx.x & (LOSS_BLOCK - 1);
+    const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);     // actions grp, grp + 4, ...
+    const int quarter = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int64_t j = (int64_t)blockIdx.x * LOSS_BLOCK + sj;
     const int64_t Mb = a.Mb_pad;
     const bool live = j < a.Mb;
+    float logp = 0.0f, kl = 0.0f;
+    // two LDS buffers in turn: a chunk is overwritten two barriers after it was read
+    for (int k0 = 0, p = 0; k0 < a.A; k0 += KC, p ^= 1) {
+#pragma unroll
+        for (int i = 0; i < KC / 4; ++i) {
+            const int q = grp + 4 * i, k = k0 + q;
+            if (k < a.A) {
+                const float ls = a.log_std[k], lso = a.log_std_old[k];
+                const float sig = expf(ls);
+                const float sig2 = expf(2.0f * ls), so2 = expf(2.0f * lso);
+                const float mu = a.mean[k * Mb + j];
+                const float d = a.act[k * Mb + j] - mu;
+                const float dm = a.mean_old[k * Mb + j] - mu;
+                sh_logp[p][q][sj] = d * d / (2.0f * sig * sig) + ls + 0.91893853320467274f;
+                sh_kl[p][q][sj] = ls - lso + (so2 + dm * dm) / (2.0f * sig2) - 0.5f;
+            }
+        }
+        __syncthreads();
+        const int n = a.A - k0 < KC ? a.A - k0 : KC;
+        if (grp == 0) {
+            for (int q = 0; q < n; ++q) logp -= sh_logp[p][q][sj];
+        } else if (grp == 2) {
+            for (int q = 0; q < n; ++q) kl += sh_kl[p][q][sj];
+        }
+    }
+    if (grp == 0) sum_logp[sj] = logp;
+    if (!live) kl = 0.0f;
+    __syncthreads();
+    logp = sum_logp[sj];
     const double n = (double)a.n_samples;
     const double amean = a.summary[IM_SUM_ADVANTAGE] / n;
     const double avar = (a.summary[IM_SUM_ADVANTAGE_SQ] - a.summary[IM_SUM_ADVANTAGE] * amean) / (n - 1.0);
     const double astd = sqrt(avar > 0.0 ? avar : 0.0);
     const float inv_mb = 1.0f / (float)a.Mb;
-    float g_logp = 0.0f, l_pi = 0.0f, l_v = 0.0f, kl = 0.0f, clipped = 0.0f;
-    float logp = 0.0f, ratio = 1.0f;
+    float g_logp = 0.0f, l_pi = 0.0f, l_v = 0.0f, clipped = 0.0f, g_v = 0.0f;
     if (live) {
-        for (int k = 0; k < a.A; ++k) {
-            const float ls = a.log_std[k];
-            const float sig = expf(ls);
-            const float d = a.act[k * Mb + j] - a.mean[k * Mb + j];
-            logp -= d * d / (2.0f * sig * sig) + ls + 0.91893853320467274f;
-        }
-        ratio = expf(logp - a.logp_old[j]);
+        const float ratio = expf(logp - a.logp_old[j]);
         const float A = (float)(((double)a.adv[j] - amean) / (astd + 1e-8));
         const float rc = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip);
         const float s1 = -A * ratio, s2 = -A * rc;
@@ -613,27 +667,16 @@ __global__ __launch_bounds__(256) void loss_kernel(LossArgs a)
             l_v = (V - R) * (V - R);
             dv = 2.0f * (V - R);
         }
-        a.dv[j] = a.value_coef * dv * inv_mb;
-        for (int k = 0; k < a.A; ++k) {
-            const float ls = a.log_std[k], lso = a.log_std_old[k];
-            const float sig2 = expf(2.0f * ls), so2 = expf(2.0f * lso);
-            const float dm = a.mean_old[k * Mb + j] - a.mean[k * Mb + j];
-            kl += ls - lso + (so2 + dm * dm) / (2.0f * sig2) - 0.5f;
-        }
-    } else if (j < Mb) {
-        a.dv[j] = 0.0f;
+        g_v = a.value_coef * dv * inv_mb;
     }
-    // Per action: the mean's gradient (bf16) and the block partial of the
-    // log-std gradient; then the four stats.  Each partial is summed over a
-    // wavefront by a fixed butterfly, and the block's four wave sums are added
-    // in wave order.
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    auto wave_sum = [](double x) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        return x;
+    auto put = [&](int f, double x) {
+        x = wave_sum63(x);
+        if (lane == 63) red[quarter][f] = x;
     };
-    for (int k = 0; k < a.A; ++k) {
+    // per action: the mean's gradient (bf16), its sum (the bias gradient) and
+    // the log-std gradient
+#pragma unroll 2
+    for (int k = grp; k < a.A; k += 4) {
         float gm = 0.0f;
         double x = 0.0;
         if (live) {
@@ -642,20 +685,28 @@ __global__ __launch_bounds__(256) void loss_kernel(LossArgs a)
             gm = g_logp * d / sig2;
             x = (double)g_logp * ((double)d * d / sig2 - 1.0);
         }
-        if (j < Mb) a.dmu[k * Mb + j] = f32_to_bf16_rne(gm);
-        x = wave_sum(x);
-        if (lane == 0) red[wave][k] = x;
+        const uint16_t h = f32_to_bf16_rne(gm);
+        a.dmu[k * Mb + j] = h;
+        put(k, x);
+        put(a.A + k, (double)bf16_to_f32(h));
     }
-    const float st[LOSS_STATS] = {l_pi, l_v, kl, clipped};
-#pragma unroll
-    for (int q = 0; q < LOSS_STATS; ++q) {
-        const double x = wave_sum(live ? (double)st[q] : 0.0);
-        if (lane == 0) red[wave][a.A + q] = x;
+    if (grp == 0) {
+        a.dv[j] = g_v;
+        put(2 * a.A, (double)g_v);
+        put(2 * a.A + 1, (double)l_pi);
+    } else if (grp == 1) {
+        put(2 * a.A + 2, (double)l_v);
+    } else if (grp == 2) {
+        put(2 * a.A + 3, (double)kl);
+    } else {
+        put(2 * a.A + 4, (double)clipped);
     }
     __syncthreads();
-    const int nf = a.A + LOSS_STATS;
-    for (int f = threadIdx.x; f < nf; f += 256)
-        a.partial[(int64_t)blockIdx.x * nf + f] = ((red[0][f] + red[1][f]) + red[2][f]) + red[3][f];
+    const int nf = loss_fields(a.A);
+    if ((int)threadIdx.x < nf) {
+        const int f = threadIdx.x;
+        a.partial[(int64_t)f * gridDim.x + blockIdx.x] = ((red[0][f] + red[1][f]) + red[2][f]) + red[3][f];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -681,15 +732,14 @@ __global__ __launch_bounds__(256) void norm_kernel(const float *__restrict__ g, 
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// the log-std gradient and loss stats of the minibatch from the loss
-// partials: one block per field, a fixed tree over the blocks' partials
+// the log-std, output-bias gradients and loss stats of the minibatch from the
+// loss partials: one block per field, a fixed tree over the blocks' partials
 __global__ __launch_bounds__(256) void loss_reduce_kernel(LossReduceArgs r)
 {
     __shared__ double red[256];
-    const int nf = r.A + LOSS_STATS;
     const int f = blockIdx.x;
     double s = 0.0;
-    for (int b = threadIdx.x; b < r.blocks; b += 256) s += r.partial[(int64_t)b * nf + f];
+    for (int b = threadIdx.x; b < r.blocks; b += 256) s += r.partial[(int64_t)f * r.blocks + b];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
@@ -698,13 +748,11 @@ __global__ __launch_bounds__(256) void loss_reduce_kernel(LossReduceArgs r)
     }
     if (threadIdx.x != 0) return;
     s = red[0];
-    if (f < r.A) {
-        r.grad_log_std[f] = (float)(s - (double)r.entropy_coef);
-    } else {
-        const int k = f - r.A;
-        const double mean = s / (double)r.Mb;
-        r.mb_stats[k] = mean;
-    }
+    const int A = r.A;
+    if (f < A) r.grad_log_std[f] = (float)(s - (double)r.entropy_coef);
+    else if (f < 2 * A) r.grad_bias[f - A] = (float)s;
+    else if (f == 2 * A) *r.grad_vbias = (float)s;
+    else r.mb_stats[f - 2 * A - 1] = s / (double)r.Mb;
 }
 
 __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs f)
@@ -771,9 +819,12 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ x, float 
 // (roll_bf16 1: bf16; 2: float32 holding the bf16-rounded value; 0:
 // float32) with its bias; padding stays zero.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void repack_kernel(RepackArgs r)
+__global__ __launch_bounds__(256) void repack_kernel(RepackMulti p)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    int l = 0;
+    while (l + 1 < p.n && (int)blockIdx.x >= p.end[l]) ++l;
+    const RepackArgs &r = p.r[l];
+    const int64_t idx = (int64_t)((int)blockIdx.x - (l ? p.end[l - 1] : 0)) * 256 + threadIdx.x;
     if (idx >= (int64_t)r.out * r.in) return;
     const int o = (int)(idx / r.in), i = (int)(idx % r.in);
     const float w = r.W[idx];
@@ -795,18 +846,24 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs r)
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-hipError_t launch_tgemm(bool bt, int epi, const TGemm &g, int splits, hipStream_t s)
+hipError_t launch_tgemm(bool bt, int epi, TGemmPair p, hipStream_t s)
 {
     // 256-row tiles of 8 waves and 256-column tiles where the shape allows
-    const bool bigm = g.M % 256 == 0, bign = tgemm_bn(g.N) == 256;
-    const int bm = bigm ? 256 : 128, bn = bign ? 256 : 128;
-    const dim3 grid((unsigned)((g.M / bm) * (g.N / bn)), (unsigned)splits);
+    const int bm = tgemm_bm(p.g[0].M), bn = tgemm_bn(p.g[0].N);
+    const bool bigm = bm == 256, bign = bn == 256;
+    int blocks[2] = {0, 0};
+    for (int k = 0; k < p.n; ++k) {
+        if (tgemm_bm(p.g[k].M) != bm || tgemm_bn(p.g[k].N) != bn) return hipErrorInvalidValue;
+        blocks[k] = (p.g[k].M / bm) * (p.g[k].N / bn) * p.splits[k];
+    }
+    p.blocks0 = blocks[0];
+    const dim3 grid((unsigned)(blocks[0] + blocks[1]));
 #define IM_TG(B, E)                                                                            \
     do {                                                                                      \
-        if (bigm && bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 256>), grid, dim3(512), 0, s, g); \
-        else if (bigm) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 128>), grid, dim3(512), 0, s, g);    \
-        else if (bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 256>), grid, dim3(256), 0, s, g);    \
-        else hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 128>), grid, dim3(256), 0, s, g);              \
+        if (bigm && bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 256>), grid, dim3(512), 0, s, p); \
+        else if (bigm) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 128>), grid, dim3(512), 0, s, p);    \
+        else if (bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 256>), grid, dim3(256), 0, s, p);    \
+        else hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 128>), grid, dim3(256), 0, s, p);              \
     } while (0)
     if (bt) {
         if (epi == T_HIDDEN) IM_TG(true, T_HIDDEN);
@@ -823,15 +880,17 @@ hipError_t launch_tgemm(bool bt, int epi, const TGemm &g, int splits, hipStream_
 
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((a.chunks_pad + 3) / 4)), dim3(256), 0, s, a);
+    const int parts = (a.K0 + GATHER_ROWS - 1) / GATHER_ROWS + 2 * ((a.A + GATHER_COLS - 1) / GATHER_COLS);
+    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((a.chunks_pad + 3) / 4), (unsigned)parts), dim3(256),
+                       0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_head_forward(const uint16_t *h, int K, int64_t Mb, const float *w, const float *b,
                                float *v, hipStream_t s)
 {
-    hipLaunchKernelGGL(head_forward_kernel, dim3((unsigned)((Mb / 8 + 255) / 256)), dim3(256), 0, s, h, K,
-                       Mb, w, b, v);
+    // Mb is a multiple of 256
+    hipLaunchKernelGGL(head_forward_kernel, dim3((unsigned)(Mb / 128)), dim3(64), 0, s, h, K, Mb, w, b, v);
     return hipGetLastError();
 }
 
@@ -844,48 +903,30 @@ hipError_t launch_head_backward(const uint16_t *h, int K, int rows, int64_t Mb, 
     return hipGetLastError();
 }
 
-hipError_t launch_rowsum(bool bf16, const void *x, int rows, int64_t Mb, const float *y, double *part,
-                         float *out, hipStream_t s)
+hipError_t launch_reduce(ReduceArgs r, hipStream_t s)
 {
-    if (rows <= 0) return hipSuccess;
-    // about 2048 blocks; segments of at least 2048 samples
-    int parts = (2048 + rows - 1) / rows;
-    while (parts > 1 && (Mb % ((int64_t)parts * 256) != 0 || Mb / parts < 2048)) --parts;
-    const dim3 grid((unsigned)rows, (unsigned)parts);
-    if (bf16)
-        hipLaunchKernelGGL(rowsum_kernel<true>, grid, dim3(256), 0, s, x, Mb, y, parts, part);
-    else
-        hipLaunchKernelGGL(rowsum_kernel<false>, grid, dim3(256), 0, s, x, Mb, y, parts, part);
-    hipLaunchKernelGGL(rowsum_finish_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, part,
-                       rows, parts, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_rowsum_finish(const double *part, int rows, int parts, float *out, hipStream_t s)
-{
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rowsum_finish_rows_kernel, dim3((unsigned)rows), dim3(256), 0, s, part, parts, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_splitk_reduce(const float *P, int S, int64_t M, int64_t N, int rows, int cols,
-                                float *out, hipStream_t s)
-{
-    const int64_t n = (int64_t)rows * cols;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, P, S, M,
-                       N, rows, cols, out);
+    int end = 0;
+    for (int k = 0; k < r.n; ++k) {
+        const ReduceJob &g = r.j[k];
+        end += (g.rows * g.cols + 255) / 256;
+        r.end[2 * k] = end;
+        end += (g.prows + 3) / 4;
+        r.end[2 * k + 1] = end;
+    }
+    if (end == 0) return hipSuccess;
+    hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)end), dim3(256), 0, s, r);
     return hipGetLastError();
 }
 
 hipError_t launch_loss(const LossArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(loss_kernel, dim3((unsigned)(a.Mb_pad / 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(loss_kernel, dim3((unsigned)(a.Mb_pad / LOSS_BLOCK)), dim3(4 * LOSS_BLOCK), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_loss_reduce(const LossReduceArgs &r, hipStream_t s)
 {
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)(r.A + LOSS_STATS)), dim3(256), 0, s, r);
+    hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)loss_fields(r.A)), dim3(256), 0, s, r);
     return hipGetLastError();
 }
 
@@ -899,17 +940,15 @@ hipError_t launch_optimizer(const float *grad, int64_t P, double *norm_partial, 
     return hipGetLastError();
 }
 
-hipError_t launch_norm(const float *grad, int64_t P, double *norm_partial, int norm_blocks,
-                       hipStream_t s)
+hipError_t launch_repack(RepackMulti r, hipStream_t s)
 {
-    hipLaunchKernelGGL(norm_kernel, dim3((unsigned)norm_blocks), dim3(256), 0, s, grad, P, norm_partial);
-    return hipGetLastError();
-}
-
-hipError_t launch_repack(const RepackArgs &r, hipStream_t s)
-{
-    const int64_t n = (int64_t)r.out * r.in;
-    hipLaunchKernelGGL(repack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, r);
+    int end = 0;
+    for (int l = 0; l < r.n; ++l) {
+        end += (int)(((int64_t)r.r[l].out * r.r[l].in + 255) / 256);
+        r.end[l] = end;
+    }
+    if (end == 0) return hipSuccess;
+    hipLaunchKernelGGL(repack_kernel, dim3((unsigned)end), dim3(256), 0, s, r);
     return hipGetLastError();
 }
 

@@ -52,12 +52,15 @@ pytestmark = pytest.mark.gpu
 G32, L32 = float(np.float32(synth.GAMMA)), float(np.float32(synth.LAMBDA))
 
 
-def _rollout(cfg, N, T, perturb=0.03):
+def _rollout(cfg, N, T, perturb=0.03, actor=None, critic=None):
     """A T-step rollout generated by the oracle (policy, critic, env step,
     GAE) with a policy whose weights are the workload's perturbed by a
     relative `perturb` (the update then starts at a KL well above zero, as
     after earlier updates); returns (world description, data dict, summary)."""
     d = synth.make_world(cfg, n_envs=N)
+    if actor is not None:
+        d["policy"] = synth.make_policy(np.random.default_rng(cfg + 5), actor, True)
+        d["critic"] = synth.make_policy(np.random.default_rng(cfg + 6), critic, True)
     w = oracle.World(d)
     pol, crit = d["policy"], d["critic"]
     rng = np.random.default_rng(cfg + 77)
@@ -355,6 +358,26 @@ def test_minibatch_gradient_stages(cfg, N, T, mbs):
         res = _gpu_minibatch(ctx, d, p, ep, mb, batch)
         _check_stages(res, d, data, _minibatch_of(perm, ep, mb, mbs), p, am, asd)
     ctx.close()
+
+
+# networks of different depths and widths: levels that only one of the two has,
+# and levels whose tile shapes differ (two launches instead of one)
+@pytest.mark.parametrize("actor,critic", [
+    ([226, 384, 256, 28], [226, 256, 512, 384, 1]),
+    ([226, 512, 128, 256, 28], [226, 512, 1]),
+    ([226, 28], [226, 256, 256, 1])])
+def test_minibatch_gradient_of_unlike_networks(actor, critic):
+    N, T = 192, 2
+    d, data, summary = _rollout(3, N, T, actor=actor, critic=critic)
+    p = dict(binding.PPO_DEFAULTS, epochs=1, minibatches=1)
+    ctx = binding.Context(d, max_envs=N)
+    ctx.ppo_setup(N * T)
+    ro = _upload(ctx, data, summary, N, T)
+    perm = _perm(1, T * N // 64, 3)
+    batch = binding.ppo_batch(ro, torch.from_numpy(perm).cuda(), torch.full((1,), 1e-3, device="cuda"))
+    res = _gpu_minibatch(ctx, d, p, 0, 0, batch)
+    am, asd = ppo.adv_stats(data["adv"])
+    _check_stages(res, d, data, _minibatch_of(perm, 0, 0, 1), p, am, asd)
 
 
 def test_adam_step_on_the_gpu_gradient():
