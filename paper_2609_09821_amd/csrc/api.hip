@@ -1277,8 +1277,8 @@ namespace im {
 struct TrainLayer {
     int out = 0, in = 0, Mp = 0, Kp = 0;   // Mp, Kp: multiples of the 128 GEMM tile
     int64_t w_off = 0, b_off = 0;          // in the parameter vector
-    uint16_t *wt = nullptr;                // [Mp][Kp] bf16
-    uint16_t *wtt = nullptr;               // [Kp][Mp] bf16
+    uint16_t *wt = nullptr;                // [Mp][Kp] bf16, in fragment order where fgemm_ok
+    uint16_t *wtt = nullptr;               // [Kp][Mp] bf16, likewise
     float *bias = nullptr;                 // [Mp]
     uint16_t *act = nullptr;               // hidden output [Mp][Mb] bf16 (null: output layer)
     uint4 *mbits = nullptr;                // its ReLU mask as bits, tile-major (Mp % 256 == 0)
@@ -1355,8 +1355,7 @@ int wgrad_tiles(const TrainLayer &L) { return (L.Mp / 128) * (wgrad_cols(L) / 12
 im_status tg(bool bt, int epi, const im::TGemm *g, const int *splits, int n, hipStream_t st)
 {
     im::TGemmPair p{};
-    const bool both = n == 2 && im::tgemm_bm(g[0].M) == im::tgemm_bm(g[1].M) &&
-                      im::tgemm_bn(g[0].N) == im::tgemm_bn(g[1].N);
+    const bool both = n == 2 && im::tgemm_bm(g[0].M) == im::tgemm_bm(g[1].M);
     for (int k = 0; k < n; k += p.n) {
         p.n = both ? 2 : 1;
         for (int q = 0; q < p.n; ++q) {
@@ -1379,13 +1378,6 @@ im_status tg(bool bt, int epi, const im::TGemm *g, const int *splits, int n, hip
         im_status s_ = (call);         \
         if (s_ != IM_OK) return s_;    \
     } while (0)
-
-// Whether a hidden layer's forward writes (and the next layer's input gradient
-// reads) its ReLU mask as bits: 256x256 tiles only.
-bool mbits_ok(const TrainLayer &L, int64_t Mb)
-{
-    return L.mbits && L.Mp % 256 == 0 && Mb % 256 == 0;
-}
 
 // forward of the GEMM layers of both networks, level by level
 im_status nets_forward(im_ctx *c, TrainState *t, int64_t Mb, hipStream_t st)
@@ -1417,7 +1409,7 @@ im_status nets_forward(im_ctx *c, TrainState *t, int64_t Mb, hipStream_t st)
                 IM_CHS(tg(true, im::T_LINEAR, &g, nullptr, 1, st));
             } else {
                 g.C = L.act;
-                g.mbits = mbits_ok(L, Mb) ? L.mbits : nullptr;
+                g.mbits = L.mbits;
                 hid[n++] = g;
             }
         }
@@ -1438,6 +1430,7 @@ im_status nets_backward(im_ctx *c, TrainState *t, int64_t Mb, int head_parts, hi
     const uint16_t *dz[2] = {t->dmu, t->dz[1][0]};
     int pp[2] = {0, 1};                 // the dz buffer the next gradient goes to
     int parts[2] = {0, head_parts};     // column blocks of the row sums in rs_tile
+    bool pairs[2] = {false, false};     // blocks of 128 columns
     for (int l = (int)std::max(t->actor.size(), t->critic.size()) - 1; l >= 0; --l) {
         im::TGemm w[2], x[2];
         int S[2], n = 0, who[2];
@@ -1478,6 +1471,7 @@ im_status nets_backward(im_ctx *c, TrainState *t, int64_t Mb, int head_parts, hi
             if (parts[k] > 0) {
                 j.part = t->rs_tile[k];
                 j.parts = parts[k];
+                j.pairs = pairs[k];
                 j.prows = L.out;
                 j.row_out = t->grad + L.b_off;
             }
@@ -1512,11 +1506,11 @@ im_status nets_backward(im_ctx *c, TrainState *t, int64_t Mb, int head_parts, hi
             h.ldc = Mb;
             h.mask = Lb.act;
             h.ldm = Mb;
-            // the mask bits the forward of layer l - 1 wrote on the same tiles
-            if (mbits_ok(Lb, Mb) && Lb.Mp == L.Kp) h.mbits = Lb.mbits;
+            h.mbits = Lb.mbits;         // null: no bits, the mask is read (Lb.Mp == L.Kp)
             h.rs_part = t->rs_tile[k];  // the bias gradient of layer l - 1, by column tile
             x[q] = h;
-            parts[k] = (int)(Mb / im::tgemm_bn(Mb));
+            parts[k] = (int)(Mb / im::tgemm_rs_bn(h.M));
+            pairs[k] = im::tgemm_rs_bn(h.M) == 128;
             dz[k] = t->dz[k][pp[k]];
             pp[k] ^= 1;
         }
@@ -1642,6 +1636,8 @@ im_status repack_all(im_ctx *c, hipStream_t st)
             r.in = L.in;
             r.wt = L.wt;
             r.wtt = L.wtt;
+            r.wt_frag = im::fgemm_ok(im::T_HIDDEN, L.Mp);
+            r.wtt_frag = im::fgemm_ok(im::T_MASK, L.Kp);
             r.Mp = L.Mp;
             r.Kp = L.Kp;
             r.roll = L.roll;
@@ -1789,7 +1785,7 @@ im_status im_ppo_setup(im_ctx *c, int64_t max_minibatch)
                 !alloc(&L.bias, sizeof(float) * L.Mp))
                 return oom();
             if (!out_layer && !alloc(&L.act, (size_t)L.Mp * Mb * 2)) return oom();
-            if (!out_layer && L.Mp % 256 == 0 && !alloc(&L.mbits, (size_t)L.Mp * Mb / 8)) return oom();
+            if (!out_layer && im::fgemm_ok(im::T_HIDDEN, L.Mp) && !alloc(&L.mbits, (size_t)L.Mp * Mb / 8)) return oom();
             // a smaller minibatch has no more splits
             const int64_t S = splitk_most(wgrad_tiles(L), Mb);
             size_t &most = sk[net == &t->critic];

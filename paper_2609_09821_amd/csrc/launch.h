@@ -110,10 +110,11 @@ hipError_t gae_scratch_address(int device, double **out);
 // PPO update (train_kernels.hip).
 enum { T_HIDDEN = 0, T_MASK = 1, T_LINEAR = 2, T_PARTIAL = 3 };
 
-// C[m][n] = sum_k A[m][k] B(k, n) over whole 128 x 128 tiles; M, N multiples
-// of 128, K and k_split of 64.
+// C[m][n] = sum_k A[m][k] B(k, n) over whole tiles; M a multiple of 128, N of
+// 256, K and k_split of 64.
 struct TGemm {
-    const uint16_t *A;   // [M][lda] bf16, k contiguous
+    const uint16_t *A;   // [M][lda] bf16, k contiguous; in fragment order (frag_index, K padded
+                         // to 64) where fgemm_ok
     int64_t lda;
     uint32_t a_bytes;
     const uint16_t *B;   // k-major [K][ldb] (n contiguous) or n-major [N][ldb]
@@ -127,10 +128,10 @@ struct TGemm {
     int64_t ldm;
     int M_valid;         // LINEAR: rows written
     double *rs_part;     // MASK, optional: per-tile row sums of the stored (masked, bf16)
-                         // output, rs_part[row * (N / tgemm_bn(N)) + column tile]
-    uint4 *mbits;        // optional, 256x256 tiles only: the sign of the stored output as
-                         // bits, tile-major.  HIDDEN writes them (bit = output > 0); MASK
-                         // reads them instead of `mask` (the bits its M x N producer wrote)
+                         // output, rs_part[row * (N / tgemm_rs_bn(M)) + column tile]
+    uint4 *mbits;        // where fgemm_ok: the sign of the stored output as bits, tile-major.
+                         // HIDDEN writes them (bit = output > 0); MASK reads them (the bits
+                         // its M x N producer wrote) instead of `mask`
 };
 
 // One or two products on the same tile shape and epilogue in one launch (the
@@ -142,9 +143,15 @@ struct TGemmPair {
     int blocks0;         // blocks of g[0] (set by the launcher)
 };
 
-// Tile of the training GEMM: rows for M rows, columns for N columns.
+// Tile rows of the training GEMMs for M rows (N is a multiple of 256).
 inline int tgemm_bm(int64_t M) { return M % 256 == 0 ? 256 : 128; }
-inline int tgemm_bn(int64_t N) { return N % 256 == 0 ? 256 : 128; }
+// Products that run on fgemm_kernel (A in fragment order, 256 x FGEMM_BN tiles):
+// the hidden layers' forward and input gradient where the output width is a
+// multiple of its 256 rows; narrower ones run on tgemm_kernel's 128 x 256 tiles.
+constexpr int FGEMM_BN = 128;
+inline bool fgemm_ok(int epi, int64_t M) { return (epi == T_HIDDEN || epi == T_MASK) && M % 256 == 0; }
+// Column blocks of the row sums a masked-gradient product leaves (rs_part).
+inline int tgemm_rs_bn(int64_t M) { return fgemm_ok(T_MASK, M) ? FGEMM_BN : 256; }
 
 struct GatherArgs {
     const float *obs;        // [T+1][D][ld]
@@ -205,6 +212,8 @@ struct ReduceJob {
     float *out;
     const double *part;
     int parts, prows;
+    int pairs;             // parts 2k and 2k + 1 (floats) are added in fp32 first: sums over 256
+                           // columns from products that leave them by 128
     float *row_out;
 };
 constexpr int MAX_REDUCE = 3;
@@ -235,6 +244,7 @@ struct RepackArgs {
     int out, in;
     uint16_t *wt;          // [out..Mp][Kp] training copy or null
     uint16_t *wtt;         // [Kp][Mp] transposed training copy or null
+    int wt_frag, wtt_frag; // that copy is in fragment order (frag_index)
     int Mp, Kp;
     void *roll;            // rollout copy [.][roll_K] or null
     int roll_K, roll_bf16; // 1: bf16, 2: fp32 of the bf16-rounded value, 0: fp32
@@ -251,7 +261,7 @@ struct RepackMulti {
     int end[MAX_REPACK];       // first block past each layer's (set by the launcher)
 };
 
-// The products of p must share the tile shape (tgemm_bm of M, tgemm_bn of N).
+// The products of p must share the tile shape (tgemm_bm of M).
 hipError_t launch_tgemm(bool bt, int epi, TGemmPair p, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 hipError_t launch_head_forward(const uint16_t *h, int K, int64_t Mb, const float *w, const float *b,

@@ -103,7 +103,7 @@ __device__ __forceinline__ int xcd_order(int b, int n)
 // four rows on distinct banks).  A split K (weight gradients: K = the
 // minibatch) takes one block per tile and split.  All operands are zero-padded to whole tiles.
 // ---------------------------------------------------------------------------
-template <bool BT, int EPI, int WM, int BN>
+template <bool BT, int EPI, int WM>
 __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
 {
     // this block's product, tile and K split: blocks of one XCD (dispatched
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
     if (second) id -= p.blocks0;
     const TGemm g = second ? p.g[1] : p.g[0];
     // WM x 2 waves, each 64 x BN/2 (TN = BN/64 MFMA tiles across); tile BM x BN
-    constexpr int NT = 128 * WM;
+    constexpr int NT = 128 * WM, BN = 256;
     constexpr int TN = BN / 64;
     constexpr int BM = 64 * WM, BK = 64, LDK = BK + 8;
     constexpr int LDN = BN + 16;                // k-major B rows (bf16)
@@ -132,13 +132,6 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
     const int kb = split * g.k_split;
     const int ke = kb + g.k_split < g.K ? kb + g.k_split : g.K;
     const int nk = (ke - kb) / BK;
-    // mask bits (256x256 tiles): the 16 pieces this thread writes in the
-    // epilogue, one byte of 8 samples each, 16 contiguous bytes per thread
-    constexpr bool MBITS = BM == 256 && BN == 256 && (EPI == T_HIDDEN || EPI == T_MASK);
-    uint4 mbits_in = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (MBITS && EPI == T_MASK)
-        if (g.mbits) mbits_in = g.mbits[(int64_t)tile * NT + tid];
-
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
         (void *)g.A, (short)0, (int)g.a_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(
@@ -269,45 +262,23 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
             }
         __syncthreads();
         // BM rows x BN/8 pieces of 8 samples
-        uint32_t mbits_out[4] = {0u, 0u, 0u, 0u};
-        const uint32_t mbits_w[4] = {mbits_in.x, mbits_in.y, mbits_in.z, mbits_in.w};
 #pragma unroll
         for (int c = 0; c < BM * BQ / NT; ++c) {
             const int v = tid + c * NT;
             const int ml = v / BQ, pc = v % BQ;
             uint4 o = *(const uint4 *)(lds + ml * LDO + pc * 8);
             const int64_t off = (m0 + ml) * g.ldc + n0 + pc * 8;
-            if constexpr (MBITS && EPI == T_HIDDEN) {
-                // bit 2k (2k+1) of the piece's byte: the low (high) half of word k is > 0
-                const uint32_t ow[4] = {o.x, o.y, o.z, o.w};
-                uint32_t byte = 0u;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t lo = ow[k] & 0xFFFFu, hi = ow[k] >> 16;
-                    byte |= ((lo != 0 && !(lo & 0x8000u)) ? 1u : 0u) << (2 * k);
-                    byte |= ((hi != 0 && !(hi & 0x8000u)) ? 1u : 0u) << (2 * k + 1);
-                }
-                mbits_out[c >> 2] |= byte << (8 * (c & 3));
-            }
             if constexpr (EPI == T_MASK) {
                 uint32_t ow[4] = {o.x, o.y, o.z, o.w};
-                if (MBITS && g.mbits) {
-                    const uint32_t byte = (mbits_w[c >> 2] >> (8 * (c & 3))) & 0xFFu;
+                const uint4 h = *(const uint4 *)(g.mask + (m0 + ml) * g.ldm + n0 + pc * 8);
+                const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        ow[k] &= ((byte >> (2 * k)) & 1u ? 0x0000FFFFu : 0u) |
-                                 ((byte >> (2 * k + 1)) & 1u ? 0xFFFF0000u : 0u);
-                } else {
-                    const uint4 h = *(const uint4 *)(g.mask + (m0 + ml) * g.ldm + n0 + pc * 8);
-                    const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        // keep each half where the activation (bf16) is > 0
-                        const uint32_t lo = hw[k] & 0xFFFFu, hi = hw[k] >> 16;
-                        const uint32_t keep = ((lo != 0 && !(lo & 0x8000u)) ? 0x0000FFFFu : 0u) |
-                                              ((hi != 0 && !(hi & 0x8000u)) ? 0xFFFF0000u : 0u);
-                        ow[k] &= keep;
-                    }
+                for (int k = 0; k < 4; ++k) {
+                    // keep each half where the activation (bf16) is > 0
+                    const uint32_t lo = hw[k] & 0xFFFFu, hi = hw[k] >> 16;
+                    const uint32_t keep = ((lo != 0 && !(lo & 0x8000u)) ? 0x0000FFFFu : 0u) |
+                                          ((hi != 0 && !(hi & 0x8000u)) ? 0xFFFF0000u : 0u);
+                    ow[k] &= keep;
                 }
                 o = make_uint4(ow[0], ow[1], ow[2], ow[3]);
                 if (g.rs_part) {
@@ -324,10 +295,6 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
             }
             *(uint4 *)((uint16_t *)g.C + off) = o;
         }
-        if constexpr (MBITS && EPI == T_HIDDEN)
-            if (g.mbits)
-                g.mbits[(int64_t)tile * NT + tid] =
-                    make_uint4(mbits_out[0], mbits_out[1], mbits_out[2], mbits_out[3]);
     } else {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -348,6 +315,219 @@ __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
                     }
             }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Forward and input-gradient products of the layers whose output width is a
+// multiple of 256: C[256 m][128 n] tiles, the weights in MFMA fragment order
+// (frag_index, K padded to 64), the k-major activations as in tgemm_kernel.
+//
+// What bounds tgemm_kernel on these shapes is LDS: a K step of a 256 x 256
+// tile reads and writes 256 KB of it for 2048 cycles of MFMA.  Here the
+// weight fragments come straight from the L2 into registers (1 KB of
+// consecutive bytes per load, one K step ahead), so that only the activations
+// pass through LDS (160 KB), and a block is 4 waves with 70 KB of LDS, two to
+// a CU: one block's epilogue (the tile staged in LDS, then 64 KB of stores)
+// runs beside the other's K loop.  A wave owns 64 rows x 128 columns (2 x 4
+// MFMA tiles), the sums over k in the order of tgemm_kernel.
+// FGEMM_FIGURES
+//
+// K loop, step kt: LDS buffer kt & 1 holds the step's activations, rb (in
+// flight) the next step's, wa the step's weight fragments.  The weight
+// fragments of step kt + 1 are loaded right after the MFMAs that used their
+// registers; rb is written to the other buffer after substep 0 (the buffer
+// was last read before the previous step's barrier) and refilled with step
+// kt + 2; the barrier after substep 2 lets substep 3 read the next step's
+// first fragments ahead of its MFMAs.  Past the last step the loads go
+// through descriptors of extent zero (no memory access).
+// ---------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void fgemm_kernel(TGemmPair p)
+{
+    constexpr int BM = 256, BN = FGEMM_BN, BK = 64, NT = 256, TN = BN / 32, BQ = BN / 8;
+    constexpr int LDN = BN + 32;      // LDS rows shifted by 64 bytes: the 4 rows x 64 bytes
+                                      // a half wave's transpose read touches lie in distinct banks
+    constexpr int STAGE = BK * LDN;
+    constexpr int LDO = BN + 8;
+    constexpr int LDS_ELEMS = BM * LDO > 2 * STAGE ? BM * LDO : 2 * STAGE;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[LDS_ELEMS];
+    int id = xcd_order(blockIdx.x, gridDim.x);
+    const bool second = id >= p.blocks0;
+    if (second) id -= p.blocks0;
+    const TGemm g = second ? p.g[1] : p.g[0];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mblocks = g.M / BM;
+    const int64_t m0 = (int64_t)(id % mblocks) * BM;
+    const int64_t n0 = (int64_t)(id / mblocks) * BN;
+    const int nk = g.K / BK;
+    uint4 mbits_in = make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (EPI == T_MASK) mbits_in = g.mbits[(int64_t)id * NT + tid];
+
+    const __amdgpu_buffer_rsrc_t ar =
+        __builtin_amdgcn_make_buffer_rsrc((void *)g.A, (short)0, (int)g.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t br =
+        __builtin_amdgcn_make_buffer_rsrc((void *)g.B, (short)0, (int)g.b_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc((void *)g.A, (short)0, 0, 0x00020000);
+
+    // weight fragments: this lane's 16 bytes of a block, and the blocks of the
+    // wave's two row tiles (4 KB per K step)
+    const uint32_t a_vo = (uint32_t)(16 * lane);
+    int a_so[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a_so[i] = ((int)(m0 / 32) + 2 * wave + i) * nk * 4096;
+    // activations: 64 rows x 16 pieces of 8 samples, 4 per thread (16 rows apart)
+    const uint32_t b_row = (uint32_t)(g.ldb * 2);
+    const uint32_t b_vo = (uint32_t)(((int64_t)(tid / BQ) * g.ldb + n0 + (tid % BQ) * 8) * 2);
+    u32x4_v wa[2][4], rb[4];
+    auto load_a = [&](const __amdgpu_buffer_rsrc_t &r, int kt, int s) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            wa[i][s] = __builtin_bit_cast(u32x4_v, __builtin_amdgcn_raw_buffer_load_b128(
+                                                       r, a_vo + 1024 * s, a_so[i] + kt * 4096, 0));
+    };
+    auto load_b = [&](const __amdgpu_buffer_rsrc_t &r, int kt) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            rb[c] = __builtin_bit_cast(u32x4_v, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    r, b_vo, (uint32_t)(kt * BK + 16 * c) * b_row, 0));
+    };
+    auto store_b = [&](int buf) {
+        uint16_t *d = lds + buf * STAGE + (tid / BQ) * LDN + (tid % BQ) * 8;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) *(u32x4_v *)(d + 16 * c * LDN) = rb[c];
+    };
+    // transpose read of the B fragments (as in tgemm_kernel)
+    const int gi = lane >> 4, si = lane & 15;
+    const int tr_off = (8 * (gi >> 1) + (si >> 2)) * LDN + 16 * (gi & 1) + 4 * (si & 3);
+    bf16x8_t bn[TN];
+    auto read_b = [&](int buf, int s) {
+        const uint16_t *q = lds + buf * STAGE + s * 16 * LDN + tr_off;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const v4s_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((IM_LDS3 v4s_t *)(q + 32 * j));
+            const v4s_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((IM_LDS3 v4s_t *)(q + 32 * j + 4 * LDN));
+            const short v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            bn[j] = __builtin_bit_cast(bf16x8_t, v8);
+        }
+    };
+
+    f32x16_t acc[2][TN];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    load_b(br, 0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) load_a(ar, 0, s);
+    store_b(0);
+    load_b(nk > 1 ? br : none, nk > 1 ? 1 : 0);
+    __syncthreads();
+    read_b(0, 0);
+    for (int kt = 0; kt < nk; ++kt) {
+        const int buf = kt & 1;
+        const bool more = kt + 1 < nk, more2 = kt + 2 < nk;
+        const __amdgpu_buffer_rsrc_t an = more ? ar : none, bnx = more2 ? br : none;
+        const int ka = more ? kt + 1 : 0, kb = more2 ? kt + 2 : 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            bf16x8_t b[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b[j] = bn[j];
+            if (s == 3) {
+                __syncthreads();
+                read_b(buf ^ 1, 0);
+            } else {
+                read_b(buf, s + 1);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        b[j], __builtin_bit_cast(bf16x8_t, wa[i][s]), acc[i][j], 0, 0, 0);
+            load_a(an, ka, s);
+            if (s == 0) {
+                store_b(buf ^ 1);
+                load_b(bnx, kb);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();
+
+    // epilogue: lane l holds row l & 31 of each 32 x 32 tile (the MFMA's first
+    // operand is the activations), registers 4*grp + q the columns
+    // 8*grp + 4*(l >> 5) + q; the half waves trade groups so that a lane holds
+    // whole 16-byte pieces of its row; the tile is staged in LDS as [m][n],
+    // then written in 16-byte pieces, 256 contiguous bytes per row
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int ml = wave * 64 + i * 32 + (lane & 31);
+        float bias = 0.0f;
+        if constexpr (EPI == T_HIDDEN) bias = g.bias[m0 + ml];
+        uint16_t *row = lds + ml * LDO + 8 * (lane >> 5);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            uint32_t w[4][2];
+#pragma unroll
+            for (int grp = 0; grp < 4; ++grp) {
+                float v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    v[q] = acc[i][j][4 * grp + q];
+                    if constexpr (EPI == T_HIDDEN) v[q] = fmaxf(v[q] + bias, 0.0f);
+                }
+                w[grp][0] = pack_bf16x2(v[0], v[1]);
+                w[grp][1] = pack_bf16x2(v[2], v[3]);
+            }
+            const auto a0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+            const auto a1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+            const auto b0 = __builtin_amdgcn_permlane32_swap(w[2][0], w[3][0], false, false);
+            const auto b1 = __builtin_amdgcn_permlane32_swap(w[2][1], w[3][1], false, false);
+            *(u32x4_v *)(row + 32 * j) = u32x4_v{a0[0], a1[0], a0[1], a1[1]};
+            *(u32x4_v *)(row + 32 * j + 16) = u32x4_v{b0[0], b1[0], b0[1], b1[1]};
+        }
+    }
+    __syncthreads();
+    // 16 pieces per thread; mask bits: word c / 4, bit 4 (c % 4) + k for the
+    // low half of the piece's word k, 16 above it for the high half
+    uint32_t mbits_out[4] = {0u, 0u, 0u, 0u};
+    const uint32_t mbits_w[4] = {mbits_in.x, mbits_in.y, mbits_in.z, mbits_in.w};
+#pragma unroll
+    for (int c = 0; c < BM * BQ / NT; ++c) {
+        const int ml = tid / BQ + c * (NT / BQ), pc = tid % BQ;
+        const uint4 o = *(const uint4 *)(lds + ml * LDO + pc * 8);
+        uint32_t ow[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int at = 4 * (c & 3) + k;
+            if constexpr (EPI == T_HIDDEN) {
+                // outputs are >= 0: bit 15 of each half becomes (half != 0)
+                const uint32_t nz = ow[k] + 0x7FFF7FFFu;
+                mbits_out[c >> 2] |= (nz >> (15 - at)) & (0x00010001u << at);
+            } else {
+                const uint32_t m = (mbits_w[c >> 2] >> at) & 0x00010001u;
+                ow[k] &= (m << 16) - m;      // 0xFFFF in each half whose bit is set
+            }
+        }
+        if constexpr (EPI == T_MASK) {
+            // the row's sum over this tile's columns, from the 16 consecutive
+            // lanes holding its pieces
+            float rs = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                rs += __uint_as_float(ow[k] << 16) + __uint_as_float(ow[k] & 0xFFFF0000u);
+            rs = lane_group_sum<BQ>(rs);
+            if (pc == BQ - 1) g.rs_part[(m0 + ml) * (g.N / BN) + n0 / BN] = (double)rs;
+        }
+        *(uint4 *)((uint16_t *)g.C + (m0 + ml) * g.ldc + n0 + pc * 8) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+    }
+    if constexpr (EPI == T_HIDDEN)
+        g.mbits[(int64_t)id * NT + tid] = make_uint4(mbits_out[0], mbits_out[1], mbits_out[2], mbits_out[3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -562,7 +742,11 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs r)
         const int row = b * 4 + (tid >> 6), lane = tid & 63;
         if (row >= g.prows) return;
         double s = 0.0;
-        for (int k = lane; k < g.parts; k += 64) s += g.part[(int64_t)row * g.parts + k];
+        const double *q = g.part + (int64_t)row * g.parts;
+        if (g.pairs)
+            for (int k = lane; k < g.parts / 2; k += 64) s += (double)((float)q[2 * k + 1] + (float)q[2 * k]);
+        else
+            for (int k = lane; k < g.parts; k += 64) s += q[k];
         s = wave_sum63(s);
         if (lane == 63) g.row_out[row] = (float)s;
         return;
@@ -829,8 +1013,8 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackMulti p)
     const int o = (int)(idx / r.in), i = (int)(idx % r.in);
     const float w = r.W[idx];
     const uint16_t h = f32_to_bf16_rne(w);
-    if (r.wt) r.wt[(int64_t)o * r.Kp + i] = h;
-    if (r.wtt) r.wtt[(int64_t)i * r.Mp + o] = h;
+    if (r.wt) r.wt[r.wt_frag ? frag_index(o, i, r.Kp / 64) : (int64_t)o * r.Kp + i] = h;
+    if (r.wtt) r.wtt[r.wtt_frag ? frag_index(i, o, r.Mp / 64) : (int64_t)i * r.Mp + o] = h;
     if (r.roll) {
         if (r.roll_bf16 == 1) ((uint16_t *)r.roll)[(int64_t)o * r.roll_K + i] = h;
         else if (r.roll_bf16 == 2) ((float *)r.roll)[(int64_t)o * r.roll_K + i] = bf16_to_f32(h);
@@ -848,33 +1032,32 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackMulti p)
 // ---------------------------------------------------------------------------
 hipError_t launch_tgemm(bool bt, int epi, TGemmPair p, hipStream_t s)
 {
-    // 256-row tiles of 8 waves and 256-column tiles where the shape allows
-    const int bm = tgemm_bm(p.g[0].M), bn = tgemm_bn(p.g[0].N);
-    const bool bigm = bm == 256, bign = bn == 256;
+    const bool frag = fgemm_ok(epi, p.g[0].M);
+    const bool bigm = tgemm_bm(p.g[0].M) == 256;
+    const int bm = bigm ? 256 : 128, bn = frag ? FGEMM_BN : 256;
     int blocks[2] = {0, 0};
     for (int k = 0; k < p.n; ++k) {
-        if (tgemm_bm(p.g[k].M) != bm || tgemm_bn(p.g[k].N) != bn) return hipErrorInvalidValue;
-        blocks[k] = (p.g[k].M / bm) * (p.g[k].N / bn) * p.splits[k];
+        const TGemm &g = p.g[k];
+        if (tgemm_bm(g.M) != bm || g.M % bm || g.N % 256 || g.K % 64) return hipErrorInvalidValue;
+        if (frag && (!g.mbits || (epi == T_MASK && !g.rs_part))) return hipErrorInvalidValue;
+        blocks[k] = (g.M / bm) * (g.N / bn) * p.splits[k];
     }
     p.blocks0 = blocks[0];
     const dim3 grid((unsigned)(blocks[0] + blocks[1]));
-#define IM_TG(B, E)                                                                            \
-    do {                                                                                      \
-        if (bigm && bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 256>), grid, dim3(512), 0, s, p); \
-        else if (bigm) hipLaunchKernelGGL((tgemm_kernel<B, E, 4, 128>), grid, dim3(512), 0, s, p);    \
-        else if (bign) hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 256>), grid, dim3(256), 0, s, p);    \
-        else hipLaunchKernelGGL((tgemm_kernel<B, E, 2, 128>), grid, dim3(256), 0, s, p);              \
-    } while (0)
-    if (bt) {
-        if (epi == T_HIDDEN) IM_TG(true, T_HIDDEN);
-        else if (epi == T_MASK) IM_TG(true, T_MASK);
-        else if (epi == T_LINEAR) IM_TG(true, T_LINEAR);
+    if (frag && bt) {
+        if (epi == T_HIDDEN) hipLaunchKernelGGL(fgemm_kernel<T_HIDDEN>, grid, dim3(256), 0, s, p);
+        else hipLaunchKernelGGL(fgemm_kernel<T_MASK>, grid, dim3(256), 0, s, p);
+    } else if (bt) {
+        if (bigm) return hipErrorInvalidValue;
+        if (epi == T_HIDDEN) hipLaunchKernelGGL((tgemm_kernel<true, T_HIDDEN, 2>), grid, dim3(256), 0, s, p);
+        else if (epi == T_MASK) hipLaunchKernelGGL((tgemm_kernel<true, T_MASK, 2>), grid, dim3(256), 0, s, p);
+        else if (epi == T_LINEAR) hipLaunchKernelGGL((tgemm_kernel<true, T_LINEAR, 2>), grid, dim3(256), 0, s, p);
         else return hipErrorInvalidValue;
     } else {
-        if (epi == T_PARTIAL) IM_TG(false, T_PARTIAL);
-        else return hipErrorInvalidValue;
+        if (epi != T_PARTIAL) return hipErrorInvalidValue;
+        if (bigm) hipLaunchKernelGGL((tgemm_kernel<false, T_PARTIAL, 4>), grid, dim3(512), 0, s, p);
+        else hipLaunchKernelGGL((tgemm_kernel<false, T_PARTIAL, 2>), grid, dim3(256), 0, s, p);
     }
-#undef IM_TG
     return hipGetLastError();
 }
 

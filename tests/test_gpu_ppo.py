@@ -374,10 +374,12 @@ def test_minibatch_gradient_of_unlike_networks(actor, critic):
     ctx.ppo_setup(N * T)
     ro = _upload(ctx, data, summary, N, T)
     perm = _perm(1, T * N // 64, 3)
-    batch = binding.ppo_batch(ro, torch.from_numpy(perm).cuda(), torch.full((1,), 1e-3, device="cuda"))
+    gperm, lr = torch.from_numpy(perm).cuda(), torch.full((1,), 1e-3, device="cuda")
+    batch = binding.ppo_batch(ro, gperm, lr)
     res = _gpu_minibatch(ctx, d, p, 0, 0, batch)
     am, asd = ppo.adv_stats(data["adv"])
     _check_stages(res, d, data, _minibatch_of(perm, 0, 0, 1), p, am, asd)
+    ctx.close()
 
 
 def test_adam_step_on_the_gpu_gradient():
