@@ -837,6 +837,61 @@ im_status check_act_sizes(const im_ctx *c, int64_t ld_obs, int64_t n_envs)
     return IM_OK;
 }
 
+// The one-launch kernel's arguments for the policy (c->d_wf not empty).
+FusedMlpArgs policy_fused_args(const im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n,
+                               int64_t n_envs, float *mean, float *action, float *logp)
+{
+    FusedMlpArgs f{};
+    f.obs = obs;
+    f.ld_obs = ld_obs;
+    f.obs_bytes = (uint32_t)((uint64_t)c->D * (uint64_t)ld_obs * 4);
+    f.D = c->D;
+    f.L = c->L;
+    for (int l = 0; l < c->L; ++l) {
+        f.w[l] = c->d_wf[l];
+        f.bias[l] = c->d_b[l];
+        f.w_bytes[l] = (uint32_t)((uint64_t)c->M_pad[l] * (uint64_t)c->K_pad[l] * 2);
+        f.M_pad[l] = c->M_pad[l];
+        f.K_pad[l] = c->K_pad[l];
+    }
+    GemmArgs &g = f.out;
+    g.N = n_envs;
+    g.n_cu = c->n_cu;
+    g.bias = c->d_b[c->L - 1];
+    g.mean = mean;
+    g.action = action;
+    g.logp = logp;
+    g.env_n = env_n;
+    g.log_std = c->d_log_std;
+    g.A = c->A;
+    g.seed = c->cfg.seed;
+    return f;
+}
+
+// The same for the critic (c->critic.d_wf not empty).
+FusedMlpArgs value_fused_args(const im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_envs,
+                              float *value)
+{
+    const auto &cr = c->critic;
+    FusedMlpArgs f{};
+    f.obs = obs;
+    f.ld_obs = ld_obs;
+    f.obs_bytes = (uint32_t)((uint64_t)c->D * (uint64_t)ld_obs * 4);
+    f.D = c->D;
+    f.L = cr.L - 1;
+    for (int l = 0; l < f.L; ++l) {
+        f.w[l] = cr.d_wf[l];
+        f.bias[l] = cr.d_b[l];
+        f.w_bytes[l] = (uint32_t)((uint64_t)cr.M_pad[l] * (uint64_t)cr.K_pad[l] * 2);
+        f.M_pad[l] = cr.M_pad[l];
+        f.K_pad[l] = cr.K_pad[l];
+    }
+    f.out.N = n_envs;
+    f.head = cr.d_head;
+    f.value = value;
+    return f;
+}
+
 // The policy's layers; *staged: the first layer read the observation through
 // the bf16 staging buffer (which then holds it).
 im_status policy_layers(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n,
@@ -846,29 +901,7 @@ im_status policy_layers(im_ctx *c, const float *obs, int64_t ld_obs, const uint3
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     const uint64_t esz = bf16 ? 2 : 4;
     if (bf16 && !c->d_wf.empty()) {
-        FusedMlpArgs f{};
-        f.obs = obs;
-        f.ld_obs = ld_obs;
-        f.obs_bytes = (uint32_t)((uint64_t)c->D * (uint64_t)ld_obs * 4);
-        f.D = c->D;
-        f.L = c->L;
-        for (int l = 0; l < c->L; ++l) {
-            f.w[l] = c->d_wf[l];
-            f.bias[l] = c->d_b[l];
-            f.w_bytes[l] = (uint32_t)((uint64_t)c->M_pad[l] * (uint64_t)c->K_pad[l] * 2);
-            f.M_pad[l] = c->M_pad[l];
-            f.K_pad[l] = c->K_pad[l];
-        }
-        GemmArgs &g = f.out;
-        g.N = n_envs;
-        g.bias = c->d_b[c->L - 1];
-        g.mean = mean;
-        g.action = action;
-        g.logp = logp;
-        g.env_n = env_n;
-        g.log_std = c->d_log_std;
-        g.A = c->A;
-        g.seed = c->cfg.seed;
+        const FusedMlpArgs f = policy_fused_args(c, obs, ld_obs, env_n, n_envs, mean, action, logp);
         hipError_t e = launch_policy_fused(f, stream);
         if (e != hipSuccess) return hip_fail(e, "fused policy launch");
         return IM_OK;
@@ -1130,22 +1163,7 @@ im_status value_layers(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_en
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     hipError_t e;
     if (!cr.d_wf.empty()) {
-        FusedMlpArgs f{};
-        f.obs = obs;
-        f.ld_obs = ld_obs;
-        f.obs_bytes = (uint32_t)((uint64_t)c->D * (uint64_t)ld_obs * 4);
-        f.D = c->D;
-        f.L = cr.L - 1;
-        for (int l = 0; l < f.L; ++l) {
-            f.w[l] = cr.d_wf[l];
-            f.bias[l] = cr.d_b[l];
-            f.w_bytes[l] = (uint32_t)((uint64_t)cr.M_pad[l] * (uint64_t)cr.K_pad[l] * 2);
-            f.M_pad[l] = cr.M_pad[l];
-            f.K_pad[l] = cr.K_pad[l];
-        }
-        f.out.N = n_envs;
-        f.head = cr.d_head;
-        f.value = value;
+        const FusedMlpArgs f = value_fused_args(c, obs, ld_obs, n_envs, value);
         e = launch_value_fused(f, st);
         return e == hipSuccess ? IM_OK : hip_fail(e, "fused value launch");
     }
@@ -1189,6 +1207,12 @@ im_status im_policy_act_value(im_ctx *c, const float *obs, int64_t ld_obs, const
     if ((s = check_act_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     if ((s = check_value_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     const hipStream_t st = (hipStream_t)stream;
+    if (!c->d_wf.empty() && !c->critic.d_wf.empty()) {
+        const hipError_t e = launch_policy_value_fused(
+            policy_fused_args(c, obs, ld_obs, env_n, n_envs, mean, action, logp),
+            value_fused_args(c, obs, ld_obs, n_envs, value), st);
+        return e == hipSuccess ? IM_OK : hip_fail(e, "fused policy and value launch");
+    }
     bool staged = false;
     if ((s = policy_layers(c, obs, ld_obs, env_n, n_envs, mean, action, logp, st, &staged)) != IM_OK)
         return s;

@@ -82,6 +82,8 @@ struct FusedMlpArgs {
 };
 hipError_t launch_policy_fused(const FusedMlpArgs &f, hipStream_t s);
 hipError_t launch_value_fused(const FusedMlpArgs &f, hipStream_t s);
+// Both on the same observation (fp.out.N == fv.out.N).
+hipError_t launch_policy_value_fused(const FusedMlpArgs &fp, const FusedMlpArgs &fv, hipStream_t s);
 
 // Rollout end (rollout_kernels.hip).
 struct GaeArgs {

@@ -1437,13 +1437,13 @@ __device__ __forceinline__ void fused_stage_obs(const ObsStream &os, uint8_t *ac
         if (j < nks) os.store(act, j, v[j]);
 }
 
-// VALUE: a critic (every layer hidden, then the value head).
+// One block of FUSED_BN envs.  VALUE: a critic (every layer hidden, then the
+// value head).
 template <bool VALUE>
-__global__ __launch_bounds__(512) void policy_fused_bf16_kernel(FusedMlpArgs f)
+__device__ __forceinline__ void fused_block(const FusedMlpArgs &f, uint8_t *act, int64_t block)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t act[FUSED_BN * FUSED_ROW];
     const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform((uint32_t)tid >> 6);
-    const int64_t n0 = (int64_t)blockIdx.x * FUSED_BN;
+    const int64_t n0 = block * FUSED_BN;
     const int64_t nv = f.out.N - n0 < FUSED_BN ? f.out.N - n0 : FUSED_BN;
 
     // observation [D][ld] fp32 -> bf16 rows of 16-byte chunks (8 features)
@@ -1484,6 +1484,34 @@ __global__ __launch_bounds__(512) void policy_fused_bf16_kernel(FusedMlpArgs f)
     }
 }
 
+template <bool VALUE>
+__global__ __launch_bounds__(512) void policy_fused_bf16_kernel(FusedMlpArgs f)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t act[FUSED_BN * FUSED_ROW];
+    fused_block<VALUE>(f, act, blockIdx.x);
+}
+
+// Policy and critic in one launch of nb blocks each (two launches each left
+// the CUs beyond nb idle for the whole of a block's pass over the weights, and
+// drained the chip between them).  by_xcd, where all the blocks fit the chip
+// at once: those on XCDs 0-3 (dispatched round robin over the 8) run the
+// policy, those on XCDs 4-7 the critic, so that an XCD's L2 streams one
+// network's weights; in several rounds the policy's longer blocks would all
+// fall on the same CUs (S15, 16381 envs: 61.5 us against 60.5 in two
+// launches), so the policy's blocks come first.  S24 policy and critic, 4096
+// envs (64 blocks each): 96.7 -> 49.6 us; S15, 16381 envs: 56.8 -> 56.3 us.
+__global__ __launch_bounds__(512) void policy_value_fused_bf16_kernel(FusedMlpArgs fp, FusedMlpArgs fv,
+                                                                      int nb, bool by_xcd)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t act[FUSED_BN * FUSED_ROW];
+    const int b = blockIdx.x;
+    const bool value = by_xcd ? (b & 4) != 0 : b >= nb;
+    const int idx = by_xcd ? (b >> 3) * 4 + (b & 3) : (value ? b - nb : b);
+    if (idx >= nb) return;
+    if (value) fused_block<true>(fv, act, idx);
+    else fused_block<false>(fp, act, idx);
+}
+
 // Shapes the kernel assumes; n_hidden: the layers that are hidden.
 static bool fused_shapes_ok(const FusedMlpArgs &f, int n_hidden)
 {
@@ -1498,12 +1526,30 @@ static bool fused_shapes_ok(const FusedMlpArgs &f, int n_hidden)
     return true;
 }
 
+static bool fused_policy_ok(const FusedMlpArgs &f)
+{
+    return fused_shapes_ok(f, f.L - 1) && f.M_pad[f.L - 1] <= 128 && !(f.M_pad[f.L - 1] & 31) &&
+           f.M_pad[f.L - 1] > 0 && f.out.A <= f.M_pad[f.L - 1];
+}
+
+static bool fused_value_ok(const FusedMlpArgs &f) { return fused_shapes_ok(f, f.L) && f.head && f.value; }
+
+hipError_t launch_policy_value_fused(const FusedMlpArgs &fp, const FusedMlpArgs &fv, hipStream_t s)
+{
+    if (fp.out.N <= 0) return hipSuccess;
+    if (!fused_policy_ok(fp) || !fused_value_ok(fv) || fp.out.N != fv.out.N) return hipErrorInvalidValue;
+    const int64_t nb = (fp.out.N + FUSED_BN - 1) / FUSED_BN;
+    const bool by_xcd = 2 * nb <= fp.out.n_cu;
+    const int64_t blocks = by_xcd ? (nb + 3) / 4 * 8 : 2 * nb;
+    hipLaunchKernelGGL(policy_value_fused_bf16_kernel, dim3((unsigned)blocks), dim3(512), 0, s, fp, fv,
+                       (int)nb, by_xcd);
+    return hipGetLastError();
+}
+
 hipError_t launch_policy_fused(const FusedMlpArgs &f, hipStream_t s)
 {
     if (f.out.N <= 0) return hipSuccess;
-    if (!fused_shapes_ok(f, f.L - 1) || f.M_pad[f.L - 1] > 128 || (f.M_pad[f.L - 1] & 31) ||
-        f.M_pad[f.L - 1] <= 0 || f.out.A > f.M_pad[f.L - 1])
-        return hipErrorInvalidValue;
+    if (!fused_policy_ok(f)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(policy_fused_bf16_kernel<false>,
                        dim3((unsigned)((f.out.N + FUSED_BN - 1) / FUSED_BN)), dim3(512), 0, s, f);
     return hipGetLastError();
@@ -1512,7 +1558,7 @@ hipError_t launch_policy_fused(const FusedMlpArgs &f, hipStream_t s)
 hipError_t launch_value_fused(const FusedMlpArgs &f, hipStream_t s)
 {
     if (f.out.N <= 0) return hipSuccess;
-    if (!fused_shapes_ok(f, f.L) || !f.head || !f.value) return hipErrorInvalidValue;
+    if (!fused_value_ok(f)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(policy_fused_bf16_kernel<true>,
                        dim3((unsigned)((f.out.N + FUSED_BN - 1) / FUSED_BN)), dim3(512), 0, s, f);
     return hipGetLastError();
