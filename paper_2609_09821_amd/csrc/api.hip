@@ -43,8 +43,14 @@ struct im_ctx {
     // bf16 policies that the one-launch policy kernel holds: each layer's
     // weights again, in MFMA fragment order (empty otherwise)
     std::vector<uint16_t *> d_wf;
+    // fp32 policies with a hidden layer: each layer's weights as three bf16
+    // planes in fragment order (layer_kernels.hip)
+    std::vector<uint16_t *> d_wp;
     float *d_log_std = nullptr;
     void *d_ws[2] = {nullptr, nullptr};
+    // the critic's activations where its layers share launches with the policy's
+    void *d_ws2[2] = {nullptr, nullptr};
+    uint16_t *d_xp = nullptr;  // the observation as the layer kernels' operand blocks
     void *d_obs16 = nullptr;   // bf16 [max_envs][K_pad[0]] staging of the observation
     size_t ws_bytes[2] = {0, 0};
     int n_cu = 0;              // compute units of the context's device
@@ -58,6 +64,7 @@ struct im_ctx {
         std::vector<float *> d_b;
         std::vector<uint16_t *> d_wf;   // bf16 critics the one-launch kernel holds: the hidden
                                         // layers' weights in MFMA fragment order (else empty)
+        std::vector<uint16_t *> d_wp;   // fp32 critics: the hidden layers' weight planes
         float *d_head = nullptr;   // [K_head + 1]: last-layer weights (zero-padded), then its bias
         int K_head = 0;            // D for a one-layer critic, else M_pad[L-2]
         int64_t bytes = 0;         // device memory of the above
@@ -93,7 +100,27 @@ bool fused_policy_fits(const im_ctx *c)
     return true;
 }
 
+// Networks that the layer kernels hold (fp32: every one with a hidden layer;
+// bf16: those of the one-launch kernel), and up to how many envs they run there.
+bool layered_policy(const im_ctx *c) { return c->L >= 2 && (!c->d_wp.empty() || !c->d_wf.empty()); }
+bool layered_critic(const im_ctx *c)
+{
+    return c->critic.L >= 2 && (!c->critic.d_wp.empty() || !c->critic.d_wf.empty());
+}
+int64_t layered_most(const im_ctx *c)
+{
+    return c->dtype == IM_DTYPE_BF16 ? im::LAYER_BF16_MAX : INT64_MAX;
+}
+
 bool finite_f(float x) { return std::isfinite(x); }
+
+// Bytes of a workspace of hidden activations `width` wide: [envs][width] of
+// the dtype, or the layer kernels' operand blocks (whole blocks of 128 envs;
+// fp32 values as three bf16 planes).
+size_t ws_size(int dtype, int64_t envs, int64_t width)
+{
+    return (size_t)round_up(envs, 128) * (size_t)width * (dtype == IM_DTYPE_BF16 ? 2 : 6);
+}
 
 bool unit_quat(const float *q, double tol)
 {
@@ -108,10 +135,16 @@ void free_critic(im_ctx *c)
     for (void *p : k.d_w) hipFree(p);
     for (float *p : k.d_b) hipFree(p);
     for (uint16_t *p : k.d_wf) hipFree(p);
+    for (uint16_t *p : k.d_wp) hipFree(p);
+    for (void *&p : c->d_ws2) {
+        hipFree(p);
+        p = nullptr;
+    }
     hipFree(k.d_head);
     k.d_w.clear();
     k.d_b.clear();
     k.d_wf.clear();
+    k.d_wp.clear();
     k.d_head = nullptr;
     k.L = 0;
     c->device_bytes -= k.bytes;
@@ -130,12 +163,45 @@ void free_ctx(im_ctx *c)
     for (void *p : c->d_w) hipFree(p);
     for (float *p : c->d_b) hipFree(p);
     for (uint16_t *p : c->d_wf) hipFree(p);
+    for (uint16_t *p : c->d_wp) hipFree(p);
     hipFree(c->d_log_std);
     hipFree(c->d_ws[0]);
     hipFree(c->d_ws[1]);
     hipFree(c->d_obs16);
+    hipFree(c->d_xp);
     delete c;
 }
+
+// fp32 weights [M_pad][K_pad] (host) into the layer kernels' three planes,
+// through one device buffer for all layers (grown as needed; the copies and
+// the packing are ordered on the null stream).
+struct PlaneUpload {
+    float *tmp = nullptr;
+    size_t bytes = 0;
+    hipError_t put(const float *w, int M_pad, int K_pad, uint16_t *planes)
+    {
+        const size_t need = (size_t)M_pad * K_pad * sizeof(float);
+        hipError_t e = hipSuccess;
+        if (need > bytes) {
+            if (tmp) e = hipFree(tmp);
+            tmp = nullptr;
+            bytes = 0;
+            if (e == hipSuccess) e = hipMalloc((void **)&tmp, need);
+            if (e != hipSuccess) return e;
+            bytes = need;
+        }
+        e = hipMemcpy(tmp, w, need, hipMemcpyHostToDevice);
+        return e == hipSuccess ? im::launch_pack_planes(tmp, M_pad, K_pad / 16, planes, nullptr) : e;
+    }
+    hipError_t done()       // waits for the packing
+    {
+        return tmp ? hipDeviceSynchronize() : hipSuccess;
+    }
+    ~PlaneUpload()
+    {
+        if (tmp) (void)hipFree(tmp);
+    }
+};
 
 template <class T>
 hipError_t dev_alloc(im_ctx *c, T **p, size_t bytes)
@@ -659,6 +725,7 @@ im_status im_create(const im_config *cfg, const im_skeleton *sk, const im_clip *
     c->M_pad.resize(c->L);
     c->K_pad.resize(c->L);
     int64_t ws_width = 0;
+    PlaneUpload planes;
     for (int l = 0; l < c->L; ++l) {
         const bool last = l == c->L - 1;
         // hidden widths padded to the 256-feature macro tile, the action width
@@ -673,16 +740,25 @@ im_status im_create(const im_config *cfg, const im_skeleton *sk, const im_clip *
                         (const uint8_t *)pol->weight[l] + (size_t)m * K * esz, (size_t)K * esz);
         std::vector<float> bbuf(c->M_pad[l], 0.0f);
         std::memcpy(bbuf.data(), pol->bias[l], sizeof(float) * M);
-        void *dw = nullptr;
+        void *dw = nullptr;     // (fp32 networks with a hidden layer run from the planes)
         float *db = nullptr;
-        IM_TRY_ALLOC(dw, wbuf.size());
+        if (pol->dtype == IM_DTYPE_BF16 || c->L < 2) {
+            IM_TRY_ALLOC(dw, wbuf.size());
+            IM_TRY_HIP(hipMemcpy(dw, wbuf.data(), wbuf.size(), hipMemcpyHostToDevice), "upload weights");
+        } else {
+            uint16_t *dwp = nullptr;
+            IM_TRY_ALLOC(dwp, wbuf.size() / 2 * 3);
+            c->d_wp.push_back(dwp);
+            IM_TRY_HIP(planes.put((const float *)wbuf.data(), c->M_pad[l], c->K_pad[l], dwp),
+                       "upload weights (planes)");
+        }
         c->d_w.push_back(dw);
         IM_TRY_ALLOC(db, sizeof(float) * bbuf.size());
         c->d_b.push_back(db);
-        IM_TRY_HIP(hipMemcpy(dw, wbuf.data(), wbuf.size(), hipMemcpyHostToDevice), "upload weights");
         IM_TRY_HIP(hipMemcpy(db, bbuf.data(), sizeof(float) * bbuf.size(), hipMemcpyHostToDevice),
                    "upload biases");
     }
+    IM_TRY_HIP(planes.done(), "pack weight planes");
     if (pol->dtype == IM_DTYPE_BF16 && fused_policy_fits(c)) {
         for (int l = 0; l < c->L; ++l) {
             const int M = c->dims[l + 1], K = c->dims[l], nks = c->K_pad[l] / 64;
@@ -703,13 +779,15 @@ im_status im_create(const im_config *cfg, const im_skeleton *sk, const im_clip *
     IM_TRY_ALLOC(c->d_partial,
                   sizeof(double) * IM_SUMMARY_FIELDS * (size_t)((max_envs + 255) / 256));
     if (c->L >= 2) {
-        const size_t wsb = (size_t)max_envs * (size_t)ws_width * esz;
+        const size_t wsb = ws_size(pol->dtype, max_envs, ws_width);
         IM_TRY_ALLOC(c->d_ws[0], wsb);
         c->ws_bytes[0] = wsb;
         if (c->L >= 3) {
             IM_TRY_ALLOC(c->d_ws[1], wsb);
             c->ws_bytes[1] = wsb;
         }
+        if (layered_policy(c))
+            IM_TRY_ALLOC(c->d_xp, ws_size(c->dtype, std::min(max_envs, layered_most(c)), c->K_pad[0]));
         // large bf16 batches of the per-layer kernels stage the observation as
         // bf16 rows for the first layer (the one-launch kernel stages it in LDS)
         if (pol->dtype == IM_DTYPE_BF16 && max_envs > SMALL_BATCH && c->d_wf.empty())
@@ -892,6 +970,81 @@ FusedMlpArgs value_fused_args(const im_ctx *c, const float *obs, int64_t ld_obs,
     return f;
 }
 
+// Hidden layers, then the sampled layer and / or the critic's head on the layer
+// kernels (layer_kernels.hip): the policy (mean not null), the critic (value
+// not null) or both.  Both together, the critic's activations go to d_ws2.
+im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n, int64_t n_envs,
+                  float *mean, float *action, float *logp, float *value, hipStream_t st)
+{
+    if (n_envs <= 0) return IM_OK;
+    const auto &cr = c->critic;
+    const int planes = c->dtype == IM_DTYPE_BF16 ? 1 : 3;
+    struct Net {
+        int hidden;
+        const std::vector<int> *M_pad, *K_pad;
+        const std::vector<uint16_t *> *w;
+        const std::vector<float *> *b;
+        void *const *ws;
+        const uint16_t *x(int l) const { return (const uint16_t *)ws[(l - 1) & 1]; }
+    };
+    Net nets[2];
+    int n = 0, levels = 0;
+    if (mean) nets[n++] = Net{c->L - 1, &c->M_pad, &c->K_pad, planes == 1 ? &c->d_wf : &c->d_wp, &c->d_b, c->d_ws};
+    if (value)
+        nets[n++] = Net{cr.L - 1, &cr.M_pad, &cr.K_pad, planes == 1 ? &cr.d_wf : &cr.d_wp, &cr.d_b,
+                        mean ? c->d_ws2 : c->d_ws};
+    for (int k = 0; k < n; ++k) levels = std::max(levels, nets[k].hidden);
+    auto layer = [&](const Net &t, int l) {
+        LayerNet a{};
+        a.x = l > 0 ? t.x(l) : c->d_xp;
+        a.w = (*t.w)[l];
+        a.bias = (*t.b)[l];
+        a.M = (*t.M_pad)[l];
+        a.K16 = (*t.K_pad)[l] / 16;
+        a.N = n_envs;
+        return a;
+    };
+    hipError_t e = im::launch_stage_planes(planes, obs, ld_obs, c->D, n_envs, (*nets[0].K_pad)[0] / 16, c->d_xp,
+                                           st);
+    if (e != hipSuccess) return hip_fail(e, "observation staging launch");
+    for (int l = 0; l < levels; ++l) {
+        LayerNet a[2];
+        int m = 0;
+        for (int k = 0; k < n; ++k)
+            if (l < nets[k].hidden) {
+                a[m] = layer(nets[k], l);
+                a[m++].y = (uint16_t *)nets[k].ws[l & 1];
+            }
+        e = im::launch_layers(planes, a, m, c->n_cu, st);
+        if (e != hipSuccess) return hip_fail(e, "layer launch");
+    }
+    LayerNet out{};
+    GemmArgs g{};
+    im::LayerHead v{};
+    if (mean) {
+        out = layer(nets[0], c->L - 1);
+        g.N = n_envs;
+        g.bias = c->d_b[c->L - 1];
+        g.mean = mean;
+        g.action = action;
+        g.logp = logp;
+        g.env_n = env_n;
+        g.log_std = c->d_log_std;
+        g.A = c->A;
+        g.seed = c->cfg.seed;
+    }
+    if (value) {
+        const Net &t = nets[n - 1];
+        v.x = t.x(t.hidden);
+        v.head = cr.d_head;
+        v.K16 = cr.K_head / 16;
+        v.N = n_envs;
+        v.value = value;
+    }
+    e = im::launch_layer_out(planes, mean ? &out : nullptr, mean ? &g : nullptr, value ? &v : nullptr, st);
+    return e == hipSuccess ? IM_OK : hip_fail(e, "output layer launch");
+}
+
 // The policy's layers; *staged: the first layer read the observation through
 // the bf16 staging buffer (which then holds it).
 im_status policy_layers(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n,
@@ -900,6 +1053,8 @@ im_status policy_layers(im_ctx *c, const float *obs, int64_t ld_obs, const uint3
 {
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     const uint64_t esz = bf16 ? 2 : 4;
+    if (layered_policy(c) && n_envs <= layered_most(c))
+        return layered(c, obs, ld_obs, env_n, n_envs, mean, action, logp, nullptr, stream);
     if (bf16 && !c->d_wf.empty()) {
         const FusedMlpArgs f = policy_fused_args(c, obs, ld_obs, env_n, n_envs, mean, action, logp);
         hipError_t e = launch_policy_fused(f, stream);
@@ -960,16 +1115,15 @@ im_status im_policy_act(im_ctx *c, const float *obs, int64_t ld_obs, const uint3
 
 namespace {
 
-// Hidden layers 0..n_hidden-1 of a packed MLP (bias, ReLU, the dtype's
-// rounding) on the observation; the last activations end in d_ws[(n_hidden-1) & 1].
+// Hidden layers 0..n_hidden-1 of a packed bf16 MLP (bias, ReLU, rounding) on
+// the observation; the last activations end in d_ws[(n_hidden-1) & 1].
 // staged: the bf16 staging buffer already holds this observation.
 im_status mlp_hidden(im_ctx *c, int n_hidden, const std::vector<int> &M_pad,
                      const std::vector<int> &K_pad, const std::vector<void *> &d_w,
                      const std::vector<float *> &d_b, const float *obs, int64_t ld_obs,
                      int64_t n_envs, hipStream_t stream, bool staged)
 {
-    const bool bf16 = c->dtype == IM_DTYPE_BF16;
-    const uint64_t esz = bf16 ? 2 : 4;
+    const uint64_t esz = 2;
     for (int l = 0; l < n_hidden; ++l) {
         GemmArgs g{};
         g.x = l == 0 ? (const void *)obs : c->d_ws[(l - 1) & 1];
@@ -987,7 +1141,7 @@ im_status mlp_hidden(im_ctx *c, int n_hidden, const std::vector<int> &M_pad,
         g.n_cu = c->n_cu;
         g.y = c->d_ws[l & 1];
         g.ld_y = M_pad[l];
-        hipError_t e = launch_policy_layer(bf16, l == 0, false, g, M_pad[l], stream);
+        hipError_t e = launch_policy_layer(true, l == 0, false, g, M_pad[l], stream);
         if (e != hipSuccess) return hip_fail(e, "hidden layer launch");
     }
     return IM_OK;
@@ -1052,6 +1206,7 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
         free_critic(c);
         return hip_fail(err, what);
     };
+    PlaneUpload planes;
     for (int l = 0; l < L - 1; ++l) {
         cr.M_pad[l] = (int)round_up(cr.dims[l + 1], 256);
         cr.K_pad[l] = l == 0 ? (int)round_up(cr.dims[0], 64) : cr.M_pad[l - 1];
@@ -1065,16 +1220,25 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
         std::memcpy(bbuf.data(), k->bias[l], sizeof(float) * M);
         void *dw = nullptr;
         float *db = nullptr;
-        if (!alloc(&dw, wbuf.size())) return oom("critic weights");
-        cr.d_w.push_back(dw);
+        if (bf16) {
+            if (!alloc(&dw, wbuf.size())) return oom("critic weights");
+            cr.d_w.push_back(dw);
+            if ((e = hipMemcpy(dw, wbuf.data(), wbuf.size(), hipMemcpyHostToDevice)) != hipSuccess)
+                return upload_fail(e, "upload critic weights");
+        } else {
+            uint16_t *dwp = nullptr;
+            if (!alloc(&dwp, wbuf.size() / 2 * 3)) return oom("critic weights");
+            cr.d_wp.push_back(dwp);
+            if ((e = planes.put((const float *)wbuf.data(), cr.M_pad[l], cr.K_pad[l], dwp)) != hipSuccess)
+                return upload_fail(e, "upload critic weights (planes)");
+        }
         if (!alloc(&db, sizeof(float) * bbuf.size())) return oom("critic biases");
         cr.d_b.push_back(db);
-        if ((e = hipMemcpy(dw, wbuf.data(), wbuf.size(), hipMemcpyHostToDevice)) != hipSuccess)
-            return upload_fail(e, "upload critic weights");
         if ((e = hipMemcpy(db, bbuf.data(), sizeof(float) * bbuf.size(), hipMemcpyHostToDevice)) !=
             hipSuccess)
             return upload_fail(e, "upload critic biases");
     }
+    if ((e = planes.done()) != hipSuccess) return upload_fail(e, "pack critic weight planes");
     // hidden layers of a bf16 critic that the one-launch kernel holds, again in
     // MFMA fragment order
     bool fits = bf16 && L >= 2 && L - 1 <= FUSED_MAX_LAYERS && cr.K_pad[0] <= FUSED_MAX_WIDTH;
@@ -1112,7 +1276,7 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
         return upload_fail(e, "upload critic head");
     // workspace for the hidden activations and the bf16 observation staging
     if (L >= 2) {
-        const size_t wsb = (size_t)c->max_envs * (size_t)ws_width * esz;
+        const size_t wsb = ws_size(c->dtype, c->max_envs, ws_width);
         if ((s = ensure_ws(c, 0, wsb)) != IM_OK || (L >= 3 && (s = ensure_ws(c, 1, wsb)) != IM_OK)) {
             free_critic(c);
             return s;
@@ -1121,6 +1285,15 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
             dev_alloc(c, &c->d_obs16, (size_t)c->max_envs * (size_t)round_up(c->D, 64) * 2) !=
                 hipSuccess)
             return oom("observation staging");
+        if (!c->d_xp && (!bf16 || !cr.d_wf.empty()) &&
+            dev_alloc(c, &c->d_xp, ws_size(c->dtype, std::min(c->max_envs, layered_most(c)), cr.K_pad[0])) !=
+                hipSuccess)
+            return oom("observation staging");
+        const int64_t most = bf16 ? LAYER_BF16_MAX : LAYER_PAIR_MAX;
+        if (layered_policy(c) && (bf16 ? !cr.d_wf.empty() : true))
+            for (int i = 0; i < (L >= 3 ? 2 : 1); ++i)
+                if (!alloc(&c->d_ws2[i], ws_size(c->dtype, std::min(c->max_envs, most), ws_width)))
+                    return oom("workspace");
     }
     cr.L = L;
     return IM_OK;
@@ -1162,6 +1335,8 @@ im_status value_layers(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_en
     const auto &cr = c->critic;
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     hipError_t e;
+    if (layered_critic(c) && n_envs <= layered_most(c))
+        return layered(c, obs, ld_obs, nullptr, n_envs, nullptr, nullptr, nullptr, value, st);
     if (!cr.d_wf.empty()) {
         const FusedMlpArgs f = value_fused_args(c, obs, ld_obs, n_envs, value);
         e = launch_value_fused(f, st);
@@ -1174,7 +1349,7 @@ im_status value_layers(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_en
         im_status s = mlp_hidden(c, cr.L - 1, cr.M_pad, cr.K_pad, cr.d_w, cr.d_b, obs, ld_obs,
                                  n_envs, st, staged);
         if (s != IM_OK) return s;
-        e = launch_value_head_rows(bf16, c->d_ws[(cr.L - 2) & 1], cr.K_head, cr.K_head, cr.d_head,
+        e = launch_value_head_rows(c->d_ws[(cr.L - 2) & 1], cr.K_head, cr.K_head, cr.d_head,
                                    cr.d_head + cr.K_head, n_envs, value, st);
     }
     return e == hipSuccess ? IM_OK : hip_fail(e, "value head launch");
@@ -1207,6 +1382,8 @@ im_status im_policy_act_value(im_ctx *c, const float *obs, int64_t ld_obs, const
     if ((s = check_act_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     if ((s = check_value_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     const hipStream_t st = (hipStream_t)stream;
+    if (layered_policy(c) && layered_critic(c) && n_envs <= std::min(layered_most(c), im::LAYER_PAIR_MAX))
+        return layered(c, obs, ld_obs, env_n, n_envs, mean, action, logp, value, st);
     if (!c->d_wf.empty() && !c->critic.d_wf.empty()) {
         const hipError_t e = launch_policy_value_fused(
             policy_fused_args(c, obs, ld_obs, env_n, n_envs, mean, action, logp),

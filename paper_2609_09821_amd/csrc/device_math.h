@@ -143,4 +143,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Block b of n -> position in an order where the blocks of one XCD (b mod 8)
+// are consecutive.
+__device__ __forceinline__ int xcd_order(int b, int n)
+{
+    const int x = b & 7, per = n >> 3, rem = n & 7;
+    return x * per + (x < rem ? x : rem) + (b >> 3);
+}
+
 }  // namespace im

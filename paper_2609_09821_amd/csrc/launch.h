@@ -85,6 +85,50 @@ hipError_t launch_value_fused(const FusedMlpArgs &f, hipStream_t s);
 // Both on the same observation (fp.out.N == fv.out.N).
 hipError_t launch_policy_value_fused(const FusedMlpArgs &fp, const FusedMlpArgs &fv, hipStream_t s);
 
+// MLP layers with both operands in fragment order (layer_kernels.hip): planes
+// = 3 for fp32 networks (every value as three bf16 planes), 1 for bf16 ones.
+// An operand of R rows (padded to 32) and 16 K16 inputs is [R/32][K16][planes]
+// blocks of 512 bf16; activation buffers hold whole blocks of 128 envs.
+struct LayerNet {
+    const uint16_t *x;   // input activations
+    const uint16_t *w;   // weights, M rows
+    const float *bias;   // [M] (hidden layers)
+    uint16_t *y;         // output activations (hidden layers)
+    int M, K16;          // M a multiple of 64 (hidden), of 32 (sampled); K16 of 4
+    int64_t N;
+};
+struct LayerPair {
+    LayerNet a[2];
+    int n;
+    int blocks0;         // blocks of a[0] (set by the launcher)
+};
+struct LayerHead {
+    const uint16_t *x;   // last hidden activations
+    const float *head;   // [16 K16 + 1] fp32 weights, then the bias
+    int K16;
+    int64_t N;
+    float *value;        // [N]
+};
+// fp32 weights [M][16 K16] (device, row-major, zero-padded) as an operand of three planes.
+hipError_t launch_pack_planes(const float *src, int M, int K16, uint16_t *w, hipStream_t s);
+// The observation [D][ld] fp32 (env fastest) as operand blocks of 16 K16 inputs.
+hipError_t launch_stage_planes(int planes, const float *obs, int64_t ld, int D, int64_t N, int K16, uint16_t *x,
+                               hipStream_t s);
+// One level of one or two networks' hidden layers.
+hipError_t launch_layers(int planes, const LayerNet *a, int n, int n_cu, hipStream_t s);
+// The policy's sampled layer (a, g) and / or the critic's head (v); null: none.
+hipError_t launch_layer_out(int planes, const LayerNet *a, const GemmArgs *g, const LayerHead *v, hipStream_t s);
+
+// Batches of a bf16 network up to this many envs run layer by layer on
+// launch_layers, which spreads a layer's weights over the chip: the one-launch
+// kernel's few blocks each stream all of them (us, S24 policy / with critic, in
+// layers and in one launch: 64 envs 23 / 23 and 51 / 51, 512 envs 30 / 41 and
+// 52 / 52, 1024 envs 41 / 63 and 52 / 52; S15 1024 envs 26 / 40 and 24 / 26).
+constexpr int64_t LAYER_BF16_MAX = 512;
+// Batches up to this many envs run the policy's and the critic's layers in
+// shared launches (above, each fills the chip alone).
+constexpr int64_t LAYER_PAIR_MAX = 8192;
+
 // Rollout end (rollout_kernels.hip).
 struct GaeArgs {
     int T;
@@ -100,8 +144,8 @@ struct GaeArgs {
     double *partial;      // [blocks][IM_SUMMARY_FIELDS] per-block sums
 };
 
-hipError_t launch_value_head_rows(bool bf16, const void *x, int64_t ld_x, int K, const float *w,
-                                  const float *bias, int64_t N, float *value, hipStream_t s);
+hipError_t launch_value_head_rows(const void *x, int64_t ld_x, int K, const float *w, const float *bias,
+                                  int64_t N, float *value, hipStream_t s);
 hipError_t launch_value_head_obs(const float *obs, int64_t ld, int D, const float *w,
                                  const float *bias, bool bf16, int64_t N, float *value, hipStream_t s);
 hipError_t launch_gae(const GaeArgs &g, hipStream_t s);

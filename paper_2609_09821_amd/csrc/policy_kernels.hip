@@ -20,31 +20,9 @@
 
 #include "device_math.h"
 #include "launch.h"
+#include "sampling.h"
 
 namespace im {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr float HALF_LOG_2PI = 0.91893853320467274f;
-
-
-// Writes n_valid*A consecutive floats from LDS to dst (16-byte stores when dst
-// is 16-byte aligned).
-template <int NTHR>
-__device__ __forceinline__ void copy_rows_out(float *dst, const float *so, int64_t cnt, int tid)
-{
-    if ((((uintptr_t)dst) & 15) == 0) {
-        const int64_t c4 = cnt >> 2;
-        for (int64_t v = tid; v < c4; v += NTHR)
-            *(f32x4_t *)(dst + 4 * v) = *(const f32x4_t *)(so + 4 * v);
-        for (int64_t v = 4 * c4 + tid; v < cnt; v += NTHR) dst[v] = so[v];
-    } else {
-        for (int64_t v = tid; v < cnt; v += NTHR) dst[v] = so[v];
-    }
-}
 
 // Epilogue of the last layer: mean = acc + b, Gaussian noise from Philox, action
 // = mean + exp(log_std) z, logp (sigma and the noise-free part of logp are
@@ -130,32 +108,30 @@ __device__ __forceinline__ void sample_epilogue(const GemmArgs &g, float *so, in
     copy_rows_out<NTHR>(g.action + n0 * A, so, nv * A, tid);
 }
 
-// fp32 layer GEMM.  Tile: WGM x WGN waves, each MT x NT MFMA tiles of 32x32
-// (v_mfma_f32_32x32x2_f32); K chunk 32.  16-byte global loads into
-// registers one chunk ahead, two LDS buffers, one barrier per chunk.  The
-// first layer reads the observation [D][ld] (env fastest) with 16-byte loads
-// along envs and transposes it into LDS.
-template <bool IN_OBS, bool SAMPLE, int WGM, int WGN, int MT, int NT>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs g)
+// fp32 policy of one layer (observation to actions; more layers run on the
+// layer kernels).  Tile: every action (MT x 32, padded) x WGN waves of 32 envs
+// (v_mfma_f32_32x32x2_f32); K chunk 32.  16-byte global loads into registers
+// ahead, two LDS buffers, one barrier per chunk.  The observation [D][ld] (env
+// fastest) is read with 16-byte loads along envs and transposed into LDS.
+template <int WGN, int MT>
+__global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
 {
-    constexpr int KC = 32;
-    constexpr int BM = WGM * MT * 32, BN = WGN * NT * 32;
-    constexpr int NTHR = 64 * WGM * WGN;
+    constexpr int KC = 32, NT = 1;
+    constexpr int BM = MT * 32, BN = WGN * NT * 32;
+    constexpr int NTHR = 64 * WGN;
     constexpr int LDA = KC + 4;                  // floats per LDS row (16-byte pad)
     constexpr int STAGE = (BM + BN) * LDA;
     constexpr int A_CH = BM * (KC / 4) / NTHR;   // float4 chunks of the weight tile per thread
-    constexpr int B_CH = BN * (KC / 4) / NTHR;   // hidden input: float4 chunks per thread
     constexpr int O_CH = KC * (BN / 4) / NTHR;   // observation: float4 (4 envs of one k) per thread
-    static_assert(BM * (KC / 4) % NTHR == 0 && BN * (KC / 4) % NTHR == 0 && KC * (BN / 4) % NTHR == 0, "split");
+    static_assert(BM * (KC / 4) % NTHR == 0 && KC * (BN / 4) % NTHR == 0, "split");
 
     // the sampling epilogue reuses the stage buffers for a BN x A output tile
-    constexpr int LDS_FLOATS = (SAMPLE && BN * BM > 2 * STAGE) ? BN * BM : 2 * STAGE;
+    constexpr int LDS_FLOATS = (BN * BM > 2 * STAGE) ? BN * BM : 2 * STAGE;
     __shared__ __attribute__((aligned(16))) float lds[LDS_FLOATS];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
+    const int wn = wave;
     const int64_t n0 = (int64_t)blockIdx.y * BN;
     const float *W = (const float *)g.w;
     const float *X = (const float *)g.x;
@@ -164,32 +140,23 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs g)
     // accumulator columns that are never stored
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
         (void *)X, (short)0, (int)g.x_bytes, 0x00020000);
-    const bool vec_obs = IN_OBS && ((g.ld_x & 3) == 0) && ((((uintptr_t)X) & 15) == 0);
-    (void)vec_obs;
+    const bool vec_obs = ((g.ld_x & 3) == 0) && ((((uintptr_t)X) & 15) == 0);
 
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
         (void *)W, (short)0, (int)g.w_bytes, 0x00020000);
     // three register stages: the global loads of chunk k+3 go out while chunk
     // k is multiplied and chunk k+1 (loaded two chunks earlier) is stored to LDS
-    constexpr int RB = IN_OBS ? O_CH : B_CH;
+    constexpr int RB = O_CH;
     f32x4_t ra0[A_CH], rb0[RB], ra1[A_CH], rb1[RB], ra2[A_CH], rb2[RB];
     auto load_global = [&](int k0, f32x4_t (&ra)[A_CH], f32x4_t (&rb)[RB]) {
 #pragma unroll
         for (int c = 0; c < A_CH; ++c) {
             const int v = tid + c * NTHR;
             const int r = v / (KC / 4), q = v % (KC / 4);
-            const uint32_t off = (uint32_t)(((m0 + r) * g.K_pad + k0 + q * 4) * 4);
+            const uint32_t off = (uint32_t)((r * g.K_pad + k0 + q * 4) * 4);
             ra[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(wr, off, 0, 0));
         }
-        if constexpr (!IN_OBS) {
-#pragma unroll
-            for (int c = 0; c < B_CH; ++c) {
-                const int v = tid + c * NTHR;
-                const int r = v / (KC / 4), q = v % (KC / 4);
-                const uint32_t off = (uint32_t)(((n0 + r) * g.ld_x + k0 + q * 4) * 4);
-                rb[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-            }
-        } else {
+        {
 #pragma unroll
             for (int c = 0; c < O_CH; ++c) {
                 const int v = tid + c * NTHR;
@@ -214,13 +181,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs g)
             const int v = tid + c * NTHR;
             *(f32x4_t *)(As + (v / (KC / 4)) * LDA + (v % (KC / 4)) * 4) = ra[c];
         }
-        if constexpr (!IN_OBS) {
-#pragma unroll
-            for (int c = 0; c < B_CH; ++c) {
-                const int v = tid + c * NTHR;
-                *(f32x4_t *)(Bs + (v / (KC / 4)) * LDA + (v % (KC / 4)) * 4) = rb[c];
-            }
-        } else {
+        {
 #pragma unroll
             for (int c = 0; c < O_CH; ++c) {
                 const int v = tid + c * NTHR;
@@ -248,7 +209,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs g)
     auto compute = [&](int buf) {
         const float *As = lds + buf * STAGE;
         const float *Bs = As + BM * LDA;
-        const int arow = wm * (MT * 32) + (lane & 31), brow = wn * (NT * 32) + (lane & 31);
+        const int arow = lane & 31, brow = wn * (NT * 32) + (lane & 31);
         const int kh = 4 * (lane >> 5);
 #pragma unroll
         for (int t = 0; t < KC / 8; ++t) {
@@ -288,111 +249,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs g)
         if (kt + 2 < nk) step(kt + 2, ra0, rb0, ra2, rb2);
     }
 
-    if constexpr (!SAMPLE) {
-        float *Y = (float *)g.y;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int64_t n = n0 + (wn * NT + j) * 32 + (lane & 31);
-                if (n >= g.N) continue;
-#pragma unroll
-                for (int grp = 0; grp < 4; ++grp) {
-                    const int64_t m = m0 + (wm * MT + i) * 32 + 8 * grp + 4 * (lane >> 5);
-                    const float4 bb = *(const float4 *)(g.bias + m);
-                    *(float4 *)(Y + n * g.ld_y + m) =
-                        make_float4(fmaxf(acc[i][j][4 * grp + 0] + bb.x, 0.0f),
-                                    fmaxf(acc[i][j][4 * grp + 1] + bb.y, 0.0f),
-                                    fmaxf(acc[i][j][4 * grp + 2] + bb.z, 0.0f),
-                                    fmaxf(acc[i][j][4 * grp + 3] + bb.w, 0.0f));
-                }
-            }
-    } else {
-        // the block covers every action (m0 == 0)
-        const int64_t nv = g.N - n0 < BN ? g.N - n0 : BN;
-        sample_epilogue<NTHR, MT, NT>(g, lds, n0, nv, wn * NT * 32, tid, acc);
-    }
-}
-
-// Last fp32 layer + sampling for small batches: one column of 32 envs and all
-// MT x 32 (padded) actions per block of SK waves, the waves splitting K.  No
-// LDS staging: for MFMA s = 4t + q of its K range a lane supplies element q of
-// a 16-byte load at k = 8t + 4 (lane / 32), for the weight row (lane % 32) and
-// the env row (lane % 32) alike, so the two halves of the wave cover k = 8t ..
-// 8t + 7 over four MFMAs.  A wave issues every load of its range before its
-// first MFMA (one memory latency instead of one per K chunk).  The partial
-// accumulators are added in LDS in wave order, then the sampling epilogue.
-template <int MT, int SK>
-__global__ __launch_bounds__(64 * SK) void sample_f32_splitk_kernel(GemmArgs g)
-{
-    constexpr int RED = (SK - 1) * MT * 16 * 64;
-    constexpr int SO = 32 * 32 * MT;    // 32 envs x M_pad >= 32 x A floats
-    constexpr int TCH = 16;             // 16-byte loads per operand row and chunk
-    __shared__ __attribute__((aligned(16))) float lds[RED > SO ? RED : SO];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t n0 = (int64_t)blockIdx.x * 32;
-    const int nt = g.K_pad / (8 * SK);  // 8-deep k groups per wave
-    const int kb = wave * nt * 8;
-    const int h = lane >> 5, r = lane & 31;
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)g.w, (short)0, (int)g.w_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)g.x, (short)0, (int)g.x_bytes, 0x00020000);
-    // env rows past N lie past the extent and read as zero
-    const uint32_t boff = (uint32_t)(((n0 + r) * g.ld_x + kb + 4 * h) * 4);
-    uint32_t aoff[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) aoff[i] = (uint32_t)(((i * 32 + r) * g.K_pad + kb + 4 * h) * 4);
-
-    f32x16_t acc[MT][1];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[i][0][q] = 0.0f;
-    for (int t0 = 0; t0 < nt; t0 += TCH) {
-        f32x4_t av[MT][TCH], bv[TCH];
-        // past the wave's range the loads are skipped and their MFMAs add zero
-#pragma unroll
-        for (int u = 0; u < TCH; ++u) {
-            const bool in = t0 + u < nt;
-            const uint32_t dk = (uint32_t)(8 * (t0 + u) * 4);
-            bv[u] = in ? __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, boff + dk, 0, 0))
-                       : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-                av[i][u] = in ? __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(wr, aoff[i] + dk, 0, 0))
-                              : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-#pragma unroll
-        for (int u = 0; u < TCH; ++u)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][u][q], bv[u][q], acc[i][0], 0, 0, 0);
-    }
-    // partial sums: waves 1.. park theirs ([wave-1][i][reg][lane]), wave 0 adds
-    // them in wave order
-    if (wave > 0) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) lds[(((wave - 1) * MT + i) * 16 + q) * 64 + lane] = acc[i][0][q];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        for (int w = 1; w < SK; ++w)
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc[i][0][q] += lds[(((w - 1) * MT + i) * 16 + q) * 64 + lane];
-    }
-    __syncthreads();
-    // every wave joins the epilogue's barriers and wide stores; only wave 0's
-    // columns are valid
-    const int64_t nv = g.N - n0 < 32 ? g.N - n0 : 32;
-    sample_epilogue<64 * SK, MT, 1>(g, lds, n0, nv, wave == 0 ? 0 : (1 << 20), tid, acc);
+    const int64_t nv = g.N - n0 < BN ? g.N - n0 : BN;
+    sample_epilogue<NTHR, MT, NT>(g, lds, n0, nv, wn * NT * 32, tid, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -700,16 +558,6 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t
                  : "=&s"(saved)
                  : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory");
-}
-
-// ReLU of a packed bf16 pair: a bf16 whose sign bit is set is a negative
-// 16-bit integer, so a packed integer max with zero clears exactly the
-// negative values (and -0).
-typedef short im_s16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t p)
-{
-    const im_s16x2_t v = __builtin_bit_cast(im_s16x2_t, p);
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, (im_s16x2_t){0, 0}));
 }
 
 // LDS byte address of a __shared__ array
@@ -1325,9 +1173,6 @@ __device__ __forceinline__ void fused_last(const FusedMlpArgs &f, uint8_t *act, 
     // units XOR-swizzled by env % 8), mean and action rows [64][A], and the
     // per-block sums of z^2 / 2 [64][33] take its place
     float *part = (float *)act;
-    float *smean = part + KS * FUSED_BN * MP;
-    float *sact = smean + FUSED_BN * A;
-    float *slp = sact + FUSED_BN * A;
     if (active) {
 #pragma unroll
         for (int nt = 0; nt < TN; ++nt) {
@@ -1355,41 +1200,8 @@ __device__ __forceinline__ void fused_last(const FusedMlpArgs &f, uint8_t *act, 
         senv[lane] = en;
     }
     __syncthreads();
-    const int G = (A + 3) / 4;
-    for (int it = tid; it < FUSED_BN * G; it += 512) {
-        const int e = it & (FUSED_BN - 1), j = it / FUSED_BN;
-        if (e >= nv) continue;
-        float mu[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mu[q] = 4 * j + q < A ? sbias[4 * j + q] : 0.0f;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            const f32x4_t v = *(const f32x4_t *)(part + (k * FUSED_BN + e) * MP + 4 * (j ^ (e & 7)));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) mu[q] += v[q];
-        }
-        float z[4];
-        normals4(g.seed, (uint32_t)(n0 + e), senv[e], (uint32_t)j, 0u, z);
-        float lp = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int m = 4 * j + q;
-            if (m < A) {
-                smean[e * A + m] = mu[q];
-                sact[e * A + m] = mu[q] + sig[m] * z[q];
-                lp += 0.5f * z[q] * z[q];
-            }
-        }
-        slp[e * 33 + j] = lp;
-    }
-    __syncthreads();
-    if (tid < nv && g.logp) {
-        float sum = 0.0f;
-        for (int j = 0; j < G; ++j) sum += slp[tid * 33 + j];
-        g.logp[n0 + tid] = -(sum + slp0);
-    }
-    copy_rows_out<512>(g.mean + n0 * A, smean, nv * A, tid);
-    copy_rows_out<512>(g.action + n0 * A, sact, nv * A, tid);
+    sample_rows<512, FUSED_BN, MP, KS>(g, part, sig, sbias, slp0, senv, n0, nv, tid,
+                                       [](float mu, int, int) { return mu; });
 }
 
 // The critic's output: v = head . h + bias over the last hidden layer's
@@ -1582,71 +1394,23 @@ static hipError_t launch_bf16_sample(const GemmArgs &g, int M_pad, hipStream_t s
     return launch_bf16_sample_t<IN_OBS, 128, 4>(g, M_pad, s);
 }
 
-// fp32 layers: 128x128 tiles (2x2 waves of 64x64) for large batches; for
-// small batches 64x64 tiles (one 32x32 MFMA tile per wave) so that a layer
-// still spreads over every SIMD.
-
-template <bool BF16, bool IN_OBS, int MT, int NT>
-static hipError_t launch_hidden_t(const GemmArgs &g, int M_pad, hipStream_t s)
-{
-    constexpr int WGM = 2, WGN = 2;
-    const dim3 grid((unsigned)(M_pad / (WGM * MT * 32)),
-                    (unsigned)((g.N + WGN * NT * 32 - 1) / (WGN * NT * 32)));
-    static_assert(!BF16, "bf16 layers use gemm_bf16_kernel");
-    hipLaunchKernelGGL((gemm_f32_kernel<IN_OBS, false, WGM, WGN, MT, NT>), grid,
-                       dim3(64 * WGM * WGN), 0, s, g);
-    return hipGetLastError();
-}
-
-template <bool BF16, bool IN_OBS>
-static hipError_t launch_hidden(const GemmArgs &g, int M_pad, hipStream_t s)
-{
-    if (g.N <= SMALL_BATCH) return launch_hidden_t<BF16, IN_OBS, 1, 1>(g, M_pad, s);
-    return launch_hidden_t<BF16, IN_OBS, 2, 2>(g, M_pad, s);
-}
-
-template <bool BF16, bool IN_OBS, int MT, int WGN>
-static hipError_t launch_sample_t(const GemmArgs &g, hipStream_t s)
-{
-    const dim3 grid(1u, (unsigned)((g.N + WGN * 32 - 1) / (WGN * 32)));
-    static_assert(!BF16, "bf16 layers use gemm_bf16_kernel");
-    hipLaunchKernelGGL((gemm_f32_kernel<IN_OBS, true, 1, WGN, MT, 1>), grid,
-                       dim3(64 * WGN), 0, s, g);
-    return hipGetLastError();
-}
-
-template <bool BF16, bool IN_OBS, int MT>
-static hipError_t launch_sample_mt(const GemmArgs &g, hipStream_t s)
-{
-    if (g.N <= SMALL_BATCH) return launch_sample_t<BF16, IN_OBS, MT, 1>(g, s);
-    return launch_sample_t<BF16, IN_OBS, MT, 4>(g, s);
-}
-
 template <int MT>
-static hipError_t launch_sample_splitk(const GemmArgs &g, hipStream_t s)
+static hipError_t launch_f32_sample_t(const GemmArgs &g, hipStream_t s)
 {
-    hipLaunchKernelGGL((sample_f32_splitk_kernel<MT, 4>), dim3((unsigned)((g.N + 31) / 32)),
-                       dim3(256), 0, s, g);
+    if (g.N <= SMALL_BATCH)
+        hipLaunchKernelGGL((gemm_f32_kernel<1, MT>), dim3(1u, (unsigned)((g.N + 31) / 32)), dim3(64), 0, s, g);
+    else
+        hipLaunchKernelGGL((gemm_f32_kernel<4, MT>), dim3(1u, (unsigned)((g.N + 127) / 128)), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 
-template <bool BF16, bool IN_OBS>
-static hipError_t launch_sample(const GemmArgs &g, int M_pad, hipStream_t s)
+static hipError_t launch_f32_sample(const GemmArgs &g, int M_pad, hipStream_t s)
 {
-    // small batches, hidden input (K_pad a multiple of 32: 8-deep groups per wave)
-    if (!IN_OBS && g.N <= SMALL_BATCH && (g.K_pad & 31) == 0) {
-        switch (M_pad / 32) {
-            case 1: return launch_sample_splitk<1>(g, s);
-            case 2: return launch_sample_splitk<2>(g, s);
-            case 3: return launch_sample_splitk<3>(g, s);
-            default: return launch_sample_splitk<4>(g, s);
-        }
-    }
     switch (M_pad / 32) {
-        case 1: return launch_sample_mt<BF16, IN_OBS, 1>(g, s);
-        case 2: return launch_sample_mt<BF16, IN_OBS, 2>(g, s);
-        case 3: return launch_sample_mt<BF16, IN_OBS, 3>(g, s);
-        default: return launch_sample_mt<BF16, IN_OBS, 4>(g, s);
+        case 1: return launch_f32_sample_t<1>(g, s);
+        case 2: return launch_f32_sample_t<2>(g, s);
+        case 3: return launch_f32_sample_t<3>(g, s);
+        default: return launch_f32_sample_t<4>(g, s);
     }
 }
 
@@ -1685,9 +1449,8 @@ hipError_t launch_policy_layer(bool bf16, bool in_obs, bool sample, const GemmAr
         }
         return in_obs ? launch_bf16_sample<true>(g, M_pad, s) : launch_bf16_sample<false>(g, M_pad, s);
     }
-    if (!sample)
-        return in_obs ? launch_hidden<false, true>(g, M_pad, s) : launch_hidden<false, false>(g, M_pad, s);
-    return in_obs ? launch_sample<false, true>(g, M_pad, s) : launch_sample<false, false>(g, M_pad, s);
+    // fp32: the one-layer policy (others run on the layer kernels)
+    return in_obs && sample ? launch_f32_sample(g, M_pad, s) : hipErrorInvalidValue;
 }
 
 }  // namespace im

@@ -46,46 +46,37 @@ hipError_t gae_scratch_address(int device, double **out)
 }
 
 // ---------------------------------------------------------------------------
-// Value head, last layer: value[e] = b[0] + sum_k w[k] x[e][k] over the last
-// hidden activations x [N][ld_x] (bf16 or fp32 rows, zero beyond the layer's
-// width).  16 lanes per env, each reading 16-byte pieces of the row (256
-// contiguous bytes per env and step of the loop); the 16 partial sums meet
-// in a fixed butterfly, so the result does not depend on timing.
+// Value head, last layer (bf16 critics outside the one-launch kernel's
+// widths): value[e] = b[0] + sum_k w[k] x[e][k] over the last hidden
+// activations x [N][ld_x] (bf16 rows, zero beyond the layer's width).  16 lanes
+// per env, each reading 16-byte pieces of the row (256 contiguous bytes per env
+// and step of the loop); the 16 partial sums meet in a fixed butterfly, so the
+// result does not depend on timing.
 // ---------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(256) void value_head_rows_kernel(const void *__restrict__ x,
+__global__ __launch_bounds__(256) void value_head_rows_kernel(const uint16_t *__restrict__ x,
                                                               int64_t ld_x, int K,
                                                               const float *__restrict__ w,
                                                               const float *__restrict__ bias,
                                                               int64_t N, float *__restrict__ value)
 {
-    constexpr int EPC = BF16 ? 8 : 4;   // elements per 16-byte piece
     const int sub = threadIdx.x & 15;
     const int64_t e = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     float acc = 0.0f;
     if (e < N) {
-        const int n_chunks = K / EPC;
-        const char *row = (const char *)x + (size_t)e * (size_t)ld_x * (BF16 ? 2 : 4);
+        const int n_chunks = K / 8;
+        const uint16_t *row = x + e * ld_x;
         for (int c = sub; c < n_chunks; c += 16) {
-            const uint4 v = *(const uint4 *)(row + (size_t)c * 16);
-            const float4 *wc = (const float4 *)(w + (size_t)c * EPC);
-            if constexpr (BF16) {
-                const float4 w0 = wc[0], w1 = wc[1];
-                acc += w0.x * bf16_to_f32((uint16_t)(v.x & 0xFFFF));
-                acc += w0.y * bf16_to_f32((uint16_t)(v.x >> 16));
-                acc += w0.z * bf16_to_f32((uint16_t)(v.y & 0xFFFF));
-                acc += w0.w * bf16_to_f32((uint16_t)(v.y >> 16));
-                acc += w1.x * bf16_to_f32((uint16_t)(v.z & 0xFFFF));
-                acc += w1.y * bf16_to_f32((uint16_t)(v.z >> 16));
-                acc += w1.z * bf16_to_f32((uint16_t)(v.w & 0xFFFF));
-                acc += w1.w * bf16_to_f32((uint16_t)(v.w >> 16));
-            } else {
-                const float4 w0 = wc[0];
-                acc += w0.x * __uint_as_float(v.x);
-                acc += w0.y * __uint_as_float(v.y);
-                acc += w0.z * __uint_as_float(v.z);
-                acc += w0.w * __uint_as_float(v.w);
-            }
+            const uint4 v = *(const uint4 *)(row + c * 8);
+            const float4 *wc = (const float4 *)(w + (size_t)c * 8);
+            const float4 w0 = wc[0], w1 = wc[1];
+            acc += w0.x * bf16_to_f32((uint16_t)(v.x & 0xFFFF));
+            acc += w0.y * bf16_to_f32((uint16_t)(v.x >> 16));
+            acc += w0.z * bf16_to_f32((uint16_t)(v.y & 0xFFFF));
+            acc += w0.w * bf16_to_f32((uint16_t)(v.y >> 16));
+            acc += w1.x * bf16_to_f32((uint16_t)(v.z & 0xFFFF));
+            acc += w1.y * bf16_to_f32((uint16_t)(v.z >> 16));
+            acc += w1.z * bf16_to_f32((uint16_t)(v.w & 0xFFFF));
+            acc += w1.w * bf16_to_f32((uint16_t)(v.w >> 16));
         }
     }
     acc += __shfl_xor(acc, 8, 16);
@@ -284,17 +275,12 @@ __global__ __launch_bounds__(256) void summary_reduce_kernel(const double *__res
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-hipError_t launch_value_head_rows(bool bf16, const void *x, int64_t ld_x, int K, const float *w,
-                                  const float *bias, int64_t N, float *value, hipStream_t s)
+hipError_t launch_value_head_rows(const void *x, int64_t ld_x, int K, const float *w, const float *bias,
+                                  int64_t N, float *value, hipStream_t s)
 {
     if (N <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((N + 15) / 16));
-    if (bf16)
-        hipLaunchKernelGGL(value_head_rows_kernel<true>, grid, dim3(256), 0, s, x, ld_x, K, w, bias,
-                           N, value);
-    else
-        hipLaunchKernelGGL(value_head_rows_kernel<false>, grid, dim3(256), 0, s, x, ld_x, K, w, bias,
-                           N, value);
+    hipLaunchKernelGGL(value_head_rows_kernel, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, s,
+                       (const uint16_t *)x, ld_x, K, w, bias, N, value);
     return hipGetLastError();
 }
 

@@ -78,14 +78,6 @@ __device__ __forceinline__ double wave_sum63(double x)
     return dpp_add<0x143, 0xC>(x);
 }
 
-// Block b of n -> position in an order where the blocks of one XCD (b mod 8)
-// are consecutive.
-__device__ __forceinline__ int xcd_order(int b, int n)
-{
-    const int x = b & 7, per = n >> 3, rem = n & 7;
-    return x * per + (x < rem ? x : rem) + (b >> 3);
-}
-
 // ---------------------------------------------------------------------------
 // GEMM: tiles of BM = 64 WM rows by BN columns (WM x 2 waves, each wave
 // 64 x BN/2 = 2 x BN/64 MFMA 32x32x16 tiles).  launch_tgemm picks WM = 4

@@ -1,0 +1,135 @@
+"""GPU tests of the layer kernels (fp32 networks as three bf16 planes, bf16
+networks on few envs): batches at the edges of their tiles and of the rules
+that choose them, odd widths, networks of unlike depth, and values that are
+not finite.
+
+The fp32 bound is derived, not measured: a layer of K inputs whose operands
+are off by dx gives sums off by at most (K + 8) 2^-24 (|W| |x| + |b|) (one
+rounding per product and addition, the products left out of the planes, the
+bias) + |W| dx, and one rounding of the result; the ReLU passes it on.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_09821_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+def _world(actor, critic, bf16, seed=7):
+    d = synth.make_world(3 if bf16 else 2, n_envs=64)
+    d["policy"] = synth.make_policy(np.random.default_rng(seed), actor, bf16)
+    d["critic"] = synth.make_policy(np.random.default_rng(seed + 1), critic, bf16)
+    return d
+
+
+def _obs(N, ld, seed=3):
+    rng = np.random.default_rng(seed)
+    return rng.standard_normal((226, ld)).astype(np.float32), rng.integers(0, 1 << 20, ld).astype(np.int32)
+
+
+def _run(ctx, obs, env_n, N, A, value=True):
+    f = dict(device="cuda", dtype=torch.float32)
+    g = [torch.from_numpy(obs).cuda(), torch.from_numpy(env_n).cuda()]
+    out = [torch.full((N, A), 7.0, **f), torch.full((N, A), 7.0, **f), torch.full((N,), 7.0, **f),
+           torch.full((N,), 7.0, **f)]
+    if value:
+        ctx.policy_act_value(g[0], g[1], N, *out)
+    else:
+        ctx.policy_act(g[0], g[1], N, *out[:3])
+        ctx.value(g[0], N, out[3])
+    torch.cuda.synchronize()
+    return [o.cpu().numpy() for o in out]
+
+
+def _bounded(net, x):
+    """float64 outputs [n][out] of an fp32 MLP and the bound above."""
+    x, dx = x.astype(np.float64), np.zeros(x.shape)
+    for l, (W, b) in enumerate(zip(net["W"], net["b"])):
+        W, b = W.astype(np.float64), b.astype(np.float64)
+        z = x @ W.T + b
+        dx = (W.shape[1] + 8) * U * (np.abs(x) @ np.abs(W).T + np.abs(b)) + dx @ np.abs(W).T + U * np.abs(z)
+        x = np.maximum(z, 0.0) if l < len(net["W"]) - 1 else z
+    return x, dx
+
+
+# 64 x 64 tiles on few and many envs, 128 x 128 tiles (4100 envs: 33 columns of
+# them), the 8-wave small kernel; odd widths; one action tile to four; a critic
+# deeper and one shallower than the policy
+@pytest.mark.parametrize("actor,critic,N,pad", [
+    ([226, 1024, 512, 28], [226, 1024, 512, 1], 1, 0),
+    ([226, 1024, 512, 28], [226, 1024, 512, 1], 33, 5),
+    ([226, 1024, 512, 28], [226, 1024, 512, 1], 1000, 0),
+    ([226, 1024, 512, 28], [226, 1024, 512, 1], 4100, 3),
+    ([226, 300, 130, 33], [226, 70, 1], 127, 0),
+    ([226, 300, 128], [226, 257, 300, 90, 1], 129, 1),
+    ([226, 500, 65], [226, 1024, 1024, 1], 2049, 0)])
+def test_fp32_layers(actor, critic, N, pad):
+    print("fp32 layers %s %s N %d" % (actor, critic, N), flush=True)
+    d = _world(actor, critic, False)
+    ctx = binding.Context(d, max_envs=N)
+    obs, env_n = _obs(N, N + pad)
+    A = actor[-1]
+    mean, action, logp, value = _run(ctx, obs, env_n, N, A)
+    for net, got in ((d["policy"], mean), (d["critic"], value[:, None])):
+        ref, bound = _bounded(net, obs[:, :N].T)
+        assert (np.abs(got - ref) <= bound).all(), float((np.abs(got - ref) / bound).max())
+    _, oa, olp = oracle.policy(d["policy"], d["config"]["seed"], obs[:, :N], env_n[:N].view(np.uint32))
+    err = np.linalg.norm(action - oa, axis=1) / np.linalg.norm(oa, axis=1)
+    assert (err <= 1e-4).all(), float(err.max())
+    assert (np.abs(logp - olp) <= 1e-5 * np.abs(olp) + 1e-4).all()
+    ctx.close()
+
+
+# both sides of the batch sizes where a network changes kernels, and where the
+# two networks stop sharing launches
+@pytest.mark.parametrize("bf16,N", [(True, 1), (True, 512), (True, 513), (False, 500), (False, 8192),
+                                    (False, 8193)])
+def test_act_value_equals_the_two_calls(bf16, N):
+    print("act_value bf16 %s N %d" % (bf16, N), flush=True)
+    d = _world([226, 1024, 512, 28], [226, 512, 256, 1], bf16)
+    ctx = binding.Context(d, max_envs=N)
+    obs, env_n = _obs(N, N)
+    a, b = _run(ctx, obs, env_n, N, 28), _run(ctx, obs, env_n, N, 28, value=False)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    if bf16:
+        om, oa, olp = oracle.policy(d["policy"], d["config"]["seed"], obs[:, :N], env_n[:N].view(np.uint32))
+        err = np.linalg.norm(a[0] - om, axis=1) / np.linalg.norm(om, axis=1)
+        assert (err <= 2e-2).all(), float(err.max())
+        ov = oracle.value(d["critic"], obs[:, :N])
+        rms = np.sqrt(np.mean(ov.astype(np.float64) ** 2))
+        assert (np.abs(a[3] - ov) <= 2e-2 * np.maximum(np.abs(ov), rms)).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("N", [40, 200, 4100])
+def test_fp32_values_that_are_not_finite(N):
+    """Infinities, NaNs and values above bf16's range in the observation and an
+    infinite weight: what fp32 arithmetic gives (a NaN is cleared by the ReLU)."""
+    print("fp32 not finite N %d" % N, flush=True)
+    d = _world([226, 256, 512, 28], [226, 256, 1], False)
+    d["policy"]["W"][1][5, 7] = np.inf
+    obs, env_n = _obs(N, N)
+    obs[3, 1], obs[200, 2], obs[17, 5], obs[225, 9], obs[0, N - 1] = np.inf, -np.inf, np.nan, 3.4e38, -3.4e38
+    obs[100, 11], obs[101, 11] = np.inf, -np.inf
+    ctx = binding.Context(d, max_envs=N)
+    mean, _, _, value = _run(ctx, obs, env_n, N, 28)
+    for net, got in ((d["policy"], mean), (d["critic"], value[:, None])):
+        x = obs.T.astype(np.float64)
+        with np.errstate(invalid="ignore", over="ignore"):
+            for l, (W, b) in enumerate(zip(net["W"], net["b"])):
+                # column by column: a BLAS product does not promise inf and NaN
+                W = W.astype(np.float64)
+                z = np.stack([(x * w).sum(axis=1) for w in W], axis=1) + b
+                x = np.fmax(z, 0.0) if l < len(net["W"]) - 1 else z
+        assert np.array_equal(np.isnan(got), np.isnan(x)) and np.array_equal(np.isinf(got), np.isinf(x))
+        inf = np.isinf(x)
+        assert np.array_equal(np.sign(got[inf]), np.sign(x[inf]))
+        fin = np.isfinite(x)
+        scale = np.abs(np.where(fin, x, 0.0)).max(axis=1, keepdims=True) + np.zeros_like(x)
+        assert (np.abs(got[fin] - x[fin]) <= 1e-4 * np.maximum(scale[fin], 1.0)).all()
+    ctx.close()
