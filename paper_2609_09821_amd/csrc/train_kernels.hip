@@ -55,29 +55,6 @@ __device__ __forceinline__ float lane_group_sum(float x)
     return x;
 }
 
-// The same over a wavefront in float64, returned in lane 63: the row sums,
-// then row 0 into row 1 and row 2 into row 3 (row broadcast of lane 15), then
-// rows 0-1 into rows 2-3 (row broadcast of lane 31).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double x)
-{
-    const int2 v = __builtin_bit_cast(int2, x);
-    int2 t;
-    t.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, ROW_MASK, 0xF, true);
-    t.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, ROW_MASK, 0xF, true);
-    return x + __builtin_bit_cast(double, t);
-}
-
-__device__ __forceinline__ double wave_sum63(double x)
-{
-    x = dpp_add<0x111, 0xF>(x);
-    x = dpp_add<0x112, 0xF>(x);
-    x = dpp_add<0x114, 0xF>(x);
-    x = dpp_add<0x118, 0xF>(x);
-    x = dpp_add<0x142, 0xA>(x);
-    return dpp_add<0x143, 0xC>(x);
-}
-
 // ---------------------------------------------------------------------------
 // GEMM: tiles of BM = 64 WM rows by BN columns (WM x 2 waves, each wave
 // 64 x BN/2 = 2 x BN/64 MFMA 32x32x16 tiles).  launch_tgemm picks WM = 4
