@@ -9,8 +9,9 @@
 // action noise.
 //
 // bf16 path: v_mfma_f32_32x32x16_bf16, the observation is rounded to bf16
-// while it is staged, hidden activations are stored as bf16.  fp32 path:
-// v_mfma_f32_32x32x2_f32 with fp32 activations.  Accumulation is fp32.
+// while it is staged, hidden activations are stored as bf16.  Accumulation is
+// fp32.  fp32 networks with a hidden layer, and bf16 ones on few envs, run on
+// layer_kernels.hip.
 //
 // The first layer reads the observation in its [D][ld] (env-fastest)
 // layout and transposes it into LDS; hidden activations are stored env-major
