@@ -56,12 +56,13 @@ CSRC = os.path.join(ROOT, "paper_2609_09821_amd", "csrc")
 SHARED_SOURCES = []
 TRAFFIC_KIB = {
     # policy: one entry per launch of im_policy_act (a bf16 policy is one launch)
-    "policy": {"sources": ["policy_kernels.hip", "device_math.h", "launch.h"], "sha": "057f2257ff61f4c1", "workloads": {
-        4: {"fetch": [109680.0], "write": [35584.0]},
-        5: {"fetch": [140414.0], "write": [58368.0]}}},
-    "env": {"sources": ["env_kernels.hip", "device_math.h", "tables.h"], "sha": "eeed804b596bf8b3", "workloads": {
-        4: {"fetch": [61765.5], "write": [169488.8]},
-        5: {"fetch": [184002.8], "write": [413742.0]}}},
+    "policy": {"sources": ["policy_kernels.hip", "sampling.h", "device_math.h", "launch.h"],
+               "sha": "09c746267e7ef256", "workloads": {
+        4: {"fetch": [109680.5], "write": [35584.0]},
+        5: {"fetch": [139063.0], "write": [58368.0]}}},
+    "env": {"sources": ["env_kernels.hip", "device_math.h", "tables.h"], "sha": "323b1be123c069b8", "workloads": {
+        4: {"fetch": [61768.1], "write": [169488.8]},
+        5: {"fetch": [184011.2], "write": [413742.9]}}},
 }
 
 
