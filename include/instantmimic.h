@@ -31,7 +31,7 @@
  * structure-of-arrays with a leading dimension `ld` (>= n_envs): component
  * c of body b of env e is at  base[(b * NC + c) * ld + e].  A context owns
  * its device copies of the skeleton, clip and weight tables and a policy
- * workspace sized for `max_envs` at creation.
+ * workspace allocated at creation, for up to `max_envs`.
  *
  * Hot calls (im_env_step_fused, im_policy_act, im_reset_envs,
  * im_standin_physics) allocate nothing, read no device memory on the host
@@ -287,7 +287,10 @@ im_status im_standin_physics(im_ctx *ctx, const im_env_bufs *bufs, float sigma_j
  * dims[L] = 1, ReLU hidden layers, linear output and the policy's dtype (the
  * same bf16 rounding points); log_std is not used and may be NULL.  Copied
  * to the device; a second call replaces the critic.  Not hot: allocates, and
- * synchronises the device; no call on the context may be in flight.
+ * synchronises the device; no call on the context may be in flight.  The
+ * policy's buffers stay where they are, also when the critic's do not fit
+ * (IM_ERR_OOM: the context is then without a critic): graphs captured from
+ * im_policy_act stay valid, those of calls with the old critic do not.
  */
 im_status im_set_critic(im_ctx *ctx, const im_policy *critic);
 

@@ -47,9 +47,8 @@ struct im_ctx {
     // planes in fragment order (layer_kernels.hip)
     std::vector<uint16_t *> d_wp;
     float *d_log_std = nullptr;
+    // hidden activations, allocated once: captured graphs hold these addresses
     void *d_ws[2] = {nullptr, nullptr};
-    // the critic's activations where its layers share launches with the policy's
-    void *d_ws2[2] = {nullptr, nullptr};
     uint16_t *d_xp = nullptr;  // the observation as the layer kernels' operand blocks
     void *d_obs16 = nullptr;   // bf16 [max_envs][K_pad[0]] staging of the observation
     size_t ws_bytes[2] = {0, 0};
@@ -67,6 +66,11 @@ struct im_ctx {
         std::vector<uint16_t *> d_wp;   // fp32 critics: the hidden layers' weight planes
         float *d_head = nullptr;   // [K_head + 1]: last-layer weights (zero-padded), then its bias
         int K_head = 0;            // D for a one-layer critic, else M_pad[L-2]
+        // hidden activations: buffers of the critic's own where the policy's are
+        // too small (null: the policy's, calls on one context being ordered), and
+        // those for layers that share launches with the policy's
+        void *d_ws[2] = {nullptr, nullptr};
+        void *d_ws_pair[2] = {nullptr, nullptr};
         int64_t bytes = 0;         // device memory of the above
     } critic;
     double *d_partial = nullptr;   // per-block summary sums, [ceil(max_envs/256)][fields]
@@ -111,6 +115,14 @@ int64_t layered_most(const im_ctx *c)
 {
     return c->dtype == IM_DTYPE_BF16 ? im::LAYER_BF16_MAX : INT64_MAX;
 }
+// Envs whose hidden activations pass through a workspace: a network that the
+// one-launch kernel holds (one_launch) leaves its larger batches to that.
+int64_t ws_envs(const im_ctx *c, bool one_launch)
+{
+    return one_launch ? std::min(c->max_envs, im::LAYER_BF16_MAX) : c->max_envs;
+}
+// Buffer i of the critic's activations, alone.
+void *critic_ws(const im_ctx *c, int i) { return c->critic.d_ws[i] ? c->critic.d_ws[i] : c->d_ws[i]; }
 
 bool finite_f(float x) { return std::isfinite(x); }
 
@@ -136,10 +148,11 @@ void free_critic(im_ctx *c)
     for (float *p : k.d_b) hipFree(p);
     for (uint16_t *p : k.d_wf) hipFree(p);
     for (uint16_t *p : k.d_wp) hipFree(p);
-    for (void *&p : c->d_ws2) {
-        hipFree(p);
-        p = nullptr;
-    }
+    for (auto *ws : {&k.d_ws, &k.d_ws_pair})
+        for (void *&p : *ws) {
+            hipFree(p);
+            p = nullptr;
+        }
     hipFree(k.d_head);
     k.d_w.clear();
     k.d_b.clear();
@@ -208,6 +221,7 @@ hipError_t dev_alloc(im_ctx *c, T **p, size_t bytes)
 {
     hipError_t e = hipMalloc((void **)p, bytes);
     if (e == hipSuccess) c->device_bytes += (int64_t)bytes;
+    else (void)hipGetLastError();   // not left for the next launch to report
     return e;
 }
 
@@ -779,7 +793,7 @@ im_status im_create(const im_config *cfg, const im_skeleton *sk, const im_clip *
     IM_TRY_ALLOC(c->d_partial,
                   sizeof(double) * IM_SUMMARY_FIELDS * (size_t)((max_envs + 255) / 256));
     if (c->L >= 2) {
-        const size_t wsb = ws_size(pol->dtype, max_envs, ws_width);
+        const size_t wsb = ws_size(pol->dtype, ws_envs(c, !c->d_wf.empty()), ws_width);
         IM_TRY_ALLOC(c->d_ws[0], wsb);
         c->ws_bytes[0] = wsb;
         if (c->L >= 3) {
@@ -972,7 +986,8 @@ FusedMlpArgs value_fused_args(const im_ctx *c, const float *obs, int64_t ld_obs,
 
 // Hidden layers, then the sampled layer and / or the critic's head on the layer
 // kernels (layer_kernels.hip): the policy (mean not null), the critic (value
-// not null) or both.  Both together, the critic's activations go to d_ws2.
+// not null) or both.  Both together, the critic's activations have buffers of
+// their own.
 im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n, int64_t n_envs,
                   float *mean, float *action, float *logp, float *value, hipStream_t st)
 {
@@ -988,11 +1003,12 @@ im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *e
         const uint16_t *x(int l) const { return (const uint16_t *)ws[(l - 1) & 1]; }
     };
     Net nets[2];
+    void *const alone[2] = {critic_ws(c, 0), critic_ws(c, 1)};
     int n = 0, levels = 0;
     if (mean) nets[n++] = Net{c->L - 1, &c->M_pad, &c->K_pad, planes == 1 ? &c->d_wf : &c->d_wp, &c->d_b, c->d_ws};
     if (value)
         nets[n++] = Net{cr.L - 1, &cr.M_pad, &cr.K_pad, planes == 1 ? &cr.d_wf : &cr.d_wp, &cr.d_b,
-                        mean ? c->d_ws2 : c->d_ws};
+                        mean ? cr.d_ws_pair : alone};
     for (int k = 0; k < n; ++k) levels = std::max(levels, nets[k].hidden);
     auto layer = [&](const Net &t, int l) {
         LayerNet a{};
@@ -1115,49 +1131,34 @@ im_status im_policy_act(im_ctx *c, const float *obs, int64_t ld_obs, const uint3
 
 namespace {
 
-// Hidden layers 0..n_hidden-1 of a packed bf16 MLP (bias, ReLU, rounding) on
-// the observation; the last activations end in d_ws[(n_hidden-1) & 1].
+// The hidden layers of a bf16 critic, one by one (bias, ReLU, rounding), on
+// the observation; the last activations end in critic_ws(c, L & 1).
 // staged: the bf16 staging buffer already holds this observation.
-im_status mlp_hidden(im_ctx *c, int n_hidden, const std::vector<int> &M_pad,
-                     const std::vector<int> &K_pad, const std::vector<void *> &d_w,
-                     const std::vector<float *> &d_b, const float *obs, int64_t ld_obs,
-                     int64_t n_envs, hipStream_t stream, bool staged)
+im_status critic_hidden(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_envs,
+                        hipStream_t stream, bool staged)
 {
+    const auto &M_pad = c->critic.M_pad, &K_pad = c->critic.K_pad;
     const uint64_t esz = 2;
-    for (int l = 0; l < n_hidden; ++l) {
+    for (int l = 0; l < c->critic.L - 1; ++l) {
         GemmArgs g{};
-        g.x = l == 0 ? (const void *)obs : c->d_ws[(l - 1) & 1];
+        g.x = l == 0 ? (const void *)obs : critic_ws(c, (l - 1) & 1);
         g.ld_x = l == 0 ? ld_obs : M_pad[l - 1];
         g.x_bytes = (uint32_t)(l == 0 ? (uint64_t)c->D * (uint64_t)ld_obs * 4
                                       : (uint64_t)n_envs * (uint64_t)M_pad[l - 1] * esz);
         g.w_bytes = (uint32_t)((uint64_t)M_pad[l] * (uint64_t)K_pad[l] * esz);
-        g.w = d_w[l];
-        g.bias = d_b[l];
+        g.w = c->critic.d_w[l];
+        g.bias = c->critic.d_b[l];
         g.K_pad = K_pad[l];
         g.K_valid = l == 0 ? c->D : K_pad[l];
         g.N = n_envs;
         g.x16 = l == 0 ? c->d_obs16 : nullptr;
         g.x16_staged = l == 0 && staged;
         g.n_cu = c->n_cu;
-        g.y = c->d_ws[l & 1];
+        g.y = critic_ws(c, l & 1);
         g.ld_y = M_pad[l];
         hipError_t e = launch_policy_layer(true, l == 0, false, g, M_pad[l], stream);
         if (e != hipSuccess) return hip_fail(e, "hidden layer launch");
     }
-    return IM_OK;
-}
-
-// Grow workspace buffer i to at least `bytes`.
-im_status ensure_ws(im_ctx *c, int i, size_t bytes)
-{
-    if (c->ws_bytes[i] >= bytes) return IM_OK;
-    hipFree(c->d_ws[i]);
-    c->device_bytes -= (int64_t)c->ws_bytes[i];
-    c->d_ws[i] = nullptr;
-    c->ws_bytes[i] = 0;
-    if (dev_alloc(c, &c->d_ws[i], bytes) != hipSuccess)
-        return fail(IM_ERR_OOM, "device allocation failed (workspace)");
-    c->ws_bytes[i] = bytes;
     return IM_OK;
 }
 
@@ -1276,11 +1277,9 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
         return upload_fail(e, "upload critic head");
     // workspace for the hidden activations and the bf16 observation staging
     if (L >= 2) {
-        const size_t wsb = ws_size(c->dtype, c->max_envs, ws_width);
-        if ((s = ensure_ws(c, 0, wsb)) != IM_OK || (L >= 3 && (s = ensure_ws(c, 1, wsb)) != IM_OK)) {
-            free_critic(c);
-            return s;
-        }
+        const size_t wsb = ws_size(c->dtype, ws_envs(c, !cr.d_wf.empty()), ws_width);
+        for (int i = 0; i < (L >= 3 ? 2 : 1); ++i)
+            if (c->ws_bytes[i] < wsb && !alloc(&cr.d_ws[i], wsb)) return oom("workspace");
         if (bf16 && c->max_envs > SMALL_BATCH && !c->d_obs16 && cr.d_wf.empty() &&
             dev_alloc(c, &c->d_obs16, (size_t)c->max_envs * (size_t)round_up(c->D, 64) * 2) !=
                 hipSuccess)
@@ -1292,7 +1291,7 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
         const int64_t most = bf16 ? LAYER_BF16_MAX : LAYER_PAIR_MAX;
         if (layered_policy(c) && (bf16 ? !cr.d_wf.empty() : true))
             for (int i = 0; i < (L >= 3 ? 2 : 1); ++i)
-                if (!alloc(&c->d_ws2[i], ws_size(c->dtype, std::min(c->max_envs, most), ws_width)))
+                if (!alloc(&cr.d_ws_pair[i], ws_size(c->dtype, std::min(c->max_envs, most), ws_width)))
                     return oom("workspace");
     }
     cr.L = L;
@@ -1346,10 +1345,9 @@ im_status value_layers(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_en
         e = launch_value_head_obs(obs, ld_obs, c->D, cr.d_head, cr.d_head + cr.K_head, bf16, n_envs,
                                   value, st);
     } else {
-        im_status s = mlp_hidden(c, cr.L - 1, cr.M_pad, cr.K_pad, cr.d_w, cr.d_b, obs, ld_obs,
-                                 n_envs, st, staged);
+        im_status s = critic_hidden(c, obs, ld_obs, n_envs, st, staged);
         if (s != IM_OK) return s;
-        e = launch_value_head_rows(c->d_ws[(cr.L - 2) & 1], cr.K_head, cr.K_head, cr.d_head,
+        e = launch_value_head_rows(critic_ws(c, cr.L & 1), cr.K_head, cr.K_head, cr.d_head,
                                    cr.d_head + cr.K_head, n_envs, value, st);
     }
     return e == hipSuccess ? IM_OK : hip_fail(e, "value head launch");
@@ -1933,7 +1931,10 @@ im_status im_ppo_setup(im_ctx *c, int64_t max_minibatch)
     t->Mb_max = Mb;
     auto alloc = [&](auto **p, size_t bytes) {
         void *q = nullptr;
-        if (hipMalloc(&q, bytes) != hipSuccess) return false;
+        if (hipMalloc(&q, bytes) != hipSuccess) {
+            (void)hipGetLastError();    // not left for the next launch to report
+            return false;
+        }
         t->allocs.push_back(q);
         t->bytes += (int64_t)bytes;
         *p = (std::remove_reference_t<decltype(*p)>)q;

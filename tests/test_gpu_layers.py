@@ -133,3 +133,70 @@ def test_fp32_values_that_are_not_finite(N):
         scale = np.abs(np.where(fin, x, 0.0)).max(axis=1, keepdims=True) + np.zeros_like(x)
         assert (np.abs(got[fin] - x[fin]) <= 1e-4 * np.maximum(scale[fin], 1.0)).all()
     ctx.close()
+
+
+def _captured(ctx, obs, env_n, N, A):
+    """A graph of policy_act on these inputs, and its outputs."""
+    f = dict(device="cuda", dtype=torch.float32)
+    g = [torch.from_numpy(obs).cuda(), torch.from_numpy(env_n).cuda()]
+    out = [torch.zeros((N, A), **f), torch.zeros((N, A), **f), torch.zeros((N,), **f)]
+    ctx.policy_act(g[0], g[1], N, *out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.policy_act(g[0], g[1], N, *out)
+    return graph, g, out
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_policy_graph_outlives_a_wider_critic(bf16):
+    """im_set_critic leaves the policy's buffers where they are: a graph of the
+    policy captured before it replays to the same bits, and writes nothing that
+    has been handed out since."""
+    N, A = 64, 28
+    print("policy graph, then a wider critic, bf16 %s" % bf16, flush=True)
+    d = _world([226, 256, 256, A], [226, 256, 1], bf16)
+    ctx = binding.Context(d, max_envs=N)
+    obs, env_n = _obs(N, N)
+    graph, g, out = _captured(ctx, obs, env_n, N, A)
+    eager = [o.clone() for o in out]
+    wide = binding.Description(_world([226, 256, 256, A], [226, 1024, 1024, 1], bf16))
+    binding.im_set_critic(ctx.ptr, wide.critic)
+    filled = [torch.full((n,), 3.0, device="cuda") for n in [1 << 14] * 64 + [1 << 20] * 32]
+    for _ in range(3):
+        for o in out:
+            o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager))
+        assert all(bool((x == 3.0).all()) for x in filled)
+    ctx.policy_act(g[0], g[1], N, *out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, eager))
+    del graph
+    ctx.close()
+
+
+def test_policy_survives_a_critic_that_does_not_fit():
+    """A critic whose workspace cannot be allocated (2^24 envs x 16384 wide: 512
+    GiB) is refused; the policy's calls go on as before."""
+    N, A = 64, 28
+    print("critic that does not fit", flush=True)
+    d = _world([226, 256, A], [226, 16384, 1], True)
+    ctx = binding.Context(d, max_envs=1 << 24, critic=False)
+    obs, env_n = _obs(N, N)
+    graph, g, out = _captured(ctx, obs, env_n, N, A)
+    eager = [o.clone() for o in out]
+    with pytest.raises(binding.ImError) as ei:
+        binding.im_set_critic(ctx.ptr, ctx.desc.critic)
+    assert ei.value.status == binding.IM_ERR_OOM
+    for call in (lambda: ctx.policy_act(g[0], g[1], N, *out), graph.replay):
+        for o in out:
+            o.zero_()
+        call()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager))
+    with pytest.raises(binding.ImError, match="no critic"):
+        ctx.value(g[0], N, out[2])
+    del graph
+    ctx.close()
