@@ -2,14 +2,21 @@
 // read from the L2 straight into registers: fp32 policies and critics, and
 // bf16 ones on small batches.
 //
-// An fp32 value is carried as three bf16 planes, x = x0 + x1 + x2 with x0 the
-// value rounded to bf16, x1 the remainder rounded, x2 the rest (exact: 8 + 8 +
-// 8 significant bits), and a product as the six plane products down to 2^-16
-// of the leading one; the three left out are below 2^-24, the size of one fp32
-// rounding.  Six v_mfma_f32_32x32x16_bf16 take 192 cycles where the eight
-// v_mfma_f32_32x32x2_f32 of the same 16 k take 512, and the fp32 accumulator
-// is rounded 6 times instead of 16.  A result that is not finite is formed
-// again with fp32 multiply-adds from the operands (slow_dot), so that
+// An fp32 value is carried as three bf16 planes, x = x0 + 2^-8 x1 + 2^-16 x2:
+// x0 the value rounded to bf16, x1 the remainder (scaled) rounded, x2 the rest
+// (8 + 8 + 8 significant bits).  With the scales every finite fp32 value,
+// subnormal or not, is its planes' sum exactly; planes of the remainders as they
+// are would leave bf16's range below 2^-110.  A product is eight plane products;
+// the ninth, x2 w2, is below 2^-32 of it (2^-30 where one factor is subnormal).
+// Products of equal scale 2^-8d have an accumulator of their own (d = 0 .. 3),
+// joined at the end (join_sums), so that the leading ones are rounded once per
+// 16 inputs and the others count fully.  Against float64, fp32 S15 at 64 to 8192
+// envs: means 1.3e-7 to 1.8e-7 off by norm (fp32 MFMA kernels 5.0e-7 to 5.2e-7,
+// six products without scales 2.1e-7 to 2.3e-7); outputs of a single product at
+// most 2^-24 off (with six, 1e-7; 1e-4 and more for operands below 1e-36).
+// Eight v_mfma_f32_32x32x16_bf16 take 256 cycles where the eight
+// v_mfma_f32_32x32x2_f32 of the same 16 k take 512.  A result that is not finite
+// is formed again with fp32 multiply-adds from the operands (slow_dot), so that
 // infinities, NaNs and overflows come out as in fp32.
 //
 // Layout: activations and weights in 1 KB blocks, one per (tile of 32 envs or
@@ -26,9 +33,12 @@ namespace im {
 
 constexpr float BF16_MAX = 3.38953139e38f, FP32_MAX = 3.402823466e38f;
 
+constexpr float PLANE = 0x1p-8f;     // scale of a plane against the one before
+
 // The bf16 planes of N values, packed in pairs (the even one in the low half).
-// Values that round to infinity take the truncated leading plane, infinities
-// and NaNs are carried by it alone.
+// Values that round to infinity take the truncated leading plane (their second
+// plane then clamped to the type's largest value, the third holds what is left),
+// infinities and NaNs are carried by it alone.
 template <int P, int N>
 __device__ __forceinline__ void split_planes(const float (&v)[N], uint32_t (&o)[P][N / 2])
 {
@@ -42,7 +52,9 @@ __device__ __forceinline__ void split_planes(const float (&v)[N], uint32_t (&o)[
 #pragma unroll
         for (int i = 0; i < N / 2; ++i) {
             float hi[2] = {__uint_as_float(o[0][i] << 16), __uint_as_float(o[0][i] & 0xFFFF0000u)};
-            float rest[2] = {v[2 * i] - hi[0], v[2 * i + 1] - hi[1]};
+            float rest[2], mid[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) rest[q] = mid[q] = (v[2 * i + q] - hi[q]) * 256.0f;
             if (big) {
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
@@ -50,25 +62,56 @@ __device__ __forceinline__ void split_planes(const float (&v)[N], uint32_t (&o)[
                     if (fabsf(x) > BF16_MAX) {
                         const bool fin = fabsf(x) <= FP32_MAX;
                         if (fin) hi[q] = __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
-                        rest[q] = fin ? x - hi[q] : 0.0f;
+                        rest[q] = fin ? (x - hi[q]) * 256.0f : 0.0f;
+                        mid[q] = fminf(fmaxf(rest[q], -BF16_MAX), BF16_MAX);
                     }
                 }
                 o[0][i] = (__float_as_uint(hi[0]) >> 16) | (__float_as_uint(hi[1]) & 0xFFFF0000u);
             }
-            o[1][i] = pack_bf16x2(rest[0], rest[1]);
-            o[2][i] = pack_bf16x2(rest[0] - __uint_as_float(o[1][i] << 16),
-                                  rest[1] - __uint_as_float(o[1][i] & 0xFFFF0000u));
+            o[1][i] = pack_bf16x2(mid[0], mid[1]);
+            o[2][i] = pack_bf16x2((rest[0] - __uint_as_float(o[1][i] << 16)) * 256.0f,
+                                  (rest[1] - __uint_as_float(o[1][i] & 0xFFFF0000u)) * 256.0f);
         }
     }
 }
 
-// Value (row, k) of an operand in fragment order: the planes' sum.
+// The fp32 value of three planes (exact).
+__device__ __forceinline__ float join_planes(float x0, float x1, float x2)
+{
+    return fmaf(x2, PLANE * PLANE, fmaf(x1, PLANE, x0));
+}
+
+// Plane products by accumulator: NG accumulators, product (weight plane,
+// input plane) into accumulator d, the sum of the two; in an order that
+// returns to an accumulator as late as possible.
+template <int P>
+struct PlaneProducts;
+template <>
+struct PlaneProducts<1> {
+    static constexpr int NG = 1, N = 1, W[1] = {0}, X[1] = {0};
+};
+template <>
+struct PlaneProducts<3> {
+    static constexpr int NG = 4, N = 8, W[8] = {2, 2, 1, 0, 1, 1, 0, 0}, X[8] = {1, 0, 0, 0, 2, 1, 1, 2};
+};
+
+// The sums of the accumulators of equal scale.
+template <int NG>
+__device__ __forceinline__ float join_sums(const float (&a)[NG])
+{
+    float s = a[NG - 1];
+#pragma unroll
+    for (int d = NG - 2; d >= 0; --d) s = fmaf(s, PLANE, a[d]);
+    return s;
+}
+
+// Value (row, k) of an operand in fragment order.
 template <int P>
 __device__ __forceinline__ float plane_value(const uint16_t *x, int K16, int64_t row, int k)
 {
     const uint16_t *q = x + (((row >> 5) * K16 + (k >> 4)) * P) * 512 + ((((k >> 3) & 1) << 5) + (row & 31)) * 8 + (k & 7);
-    float v = bf16_to_f32(q[0]);
-    if constexpr (P == 3) v = (v + bf16_to_f32(q[512])) + bf16_to_f32(q[1024]);
+    const float v = bf16_to_f32(q[0]);
+    if constexpr (P == 3) return join_planes(v, bf16_to_f32(q[512]), bf16_to_f32(q[1024]));
     return v;
 }
 
@@ -132,18 +175,25 @@ __global__ __launch_bounds__(256) void pack_planes_kernel(const float *__restric
         *((u32x4_t *)(w + (b * 3 + p) * 512) + lane) = u32x4_t{o[p][0], o[p][1], o[p][2], o[p][3]};
 }
 
-// acc[TM][TN] += W[TM 32][k] X[TN 32][k]^T over the 16-input steps k0 .. k1-1
-// of the weight tiles from mt0 and env tiles from nt0.  U steps of operands
-// are loaded at a time, two such sets in turn, so that one is in flight while
-// the other is multiplied (steps past the end load the last one again).
-template <int P, int TM, int TN, int U>
-__device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt0, int k0, int k1,
-                                          int lane, f32x16_t (&acc)[TM][TN])
+// out[i] = W[32][k] X[32][k]^T of weight tile mt0 + i and env tile nt over the
+// 16-input steps k0 .. k1-1.  U steps of operands are loaded at a time, two such
+// sets in turn, so that one is in flight while the other is multiplied (steps
+// past the end load the last one again).
+template <int P, int TM, int U>
+__device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt, int k0, int k1,
+                                          int lane, f32x16_t (&out)[TM])
 {
+    using Prod = PlaneProducts<P>;
     struct Set {
-        u32x4_t w[U][TM][P], x[U][TN][P];
+        u32x4_t w[U][TM][P], x[U][P];
     };
-    if (k0 >= k1) return;
+    f32x16_t acc[Prod::NG][TM];
+#pragma unroll
+    for (int d = 0; d < Prod::NG; ++d)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[d][i][q] = 0.0f;
     auto load = [&](int k, Set &t) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -153,9 +203,7 @@ __device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
                     t.w[u][i][p] = *((const u32x4_t *)(a.w + ((int64_t)((mt0 + i) * a.K16 + s) * P + p) * 512) + lane);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    t.x[u][j][p] = *((const u32x4_t *)(a.x + (((nt0 + j) * a.K16 + s) * P + p) * 512) + lane);
+                t.x[u][p] = *((const u32x4_t *)(a.x + ((nt * a.K16 + s) * P + p) * 512) + lane);
             }
         }
     };
@@ -163,31 +211,39 @@ __device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (k + u >= k1) break;
-            // smallest products first
 #pragma unroll
-            for (int d = P - 1; d >= 0; --d)
+            for (int c = 0; c < Prod::N; ++c)
 #pragma unroll
-                for (int pw = d; pw >= 0; --pw)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(bf16x8_t, t.w[u][i][pw]),
-                                __builtin_bit_cast(bf16x8_t, t.x[u][j][d - pw]), acc[i][j], 0, 0, 0);
+                for (int i = 0; i < TM; ++i) {
+                    f32x16_t &t16 = acc[Prod::W[c] + Prod::X[c]][i];
+                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8_t, t.w[u][i][Prod::W[c]]),
+                        __builtin_bit_cast(bf16x8_t, t.x[u][Prod::X[c]]), t16, 0, 0, 0);
+                }
         }
     };
     // (scheduling barriers keep the loads ahead of the products)
-    Set ta, tb;
-    load(k0, ta);
-    for (int k = k0; k < k1; k += 2 * U) {
-        load(k + U, tb);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(k, ta);
-        load(k + 2 * U, ta);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(k + U, tb);
+    if (k0 < k1) {
+        Set ta, tb;
+        load(k0, ta);
+        for (int k = k0; k < k1; k += 2 * U) {
+            if (k + U < k1) load(k + U, tb);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(k, ta);
+            if (k + 2 * U < k1) load(k + 2 * U, ta);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(k + U, tb);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            float t[Prod::NG];
+#pragma unroll
+            for (int d = 0; d < Prod::NG; ++d) t[d] = acc[d][i][q];
+            out[i][q] = join_sums<Prod::NG>(t);
+        }
 }
 
 // The sums v of tile (mt, nt) (lane: env l & 31, register 4 grp + q: feature
@@ -265,14 +321,12 @@ __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
         bias[grp] = *(const float4 *)(a.bias + 32 * mt + 8 * grp + 4 * (lane >> 5));
-    f32x16_t acc[1][1];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[0][0][q] = 0.0f;
-    layer_mma<P, 1, 1, U>(a, mt, nt, wave * a.K16 / WK, (wave + 1) * a.K16 / WK, lane, acc);
+    f32x16_t acc[1];
+    layer_mma<P, 1, U>(a, mt, nt, wave * a.K16 / WK, (wave + 1) * a.K16 / WK, lane, acc);
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
         red[wave][grp][lane] =
-            f32x4_t{acc[0][0][4 * grp], acc[0][0][4 * grp + 1], acc[0][0][4 * grp + 2], acc[0][0][4 * grp + 3]};
+            f32x4_t{acc[0][4 * grp], acc[0][4 * grp + 1], acc[0][4 * grp + 2], acc[0][4 * grp + 3]};
     __syncthreads();
     if (wave > 0) return;
     float v[16];
@@ -310,25 +364,27 @@ __device__ __forceinline__ void phase_order()
     }
 }
 
-// The same on many envs, fp32: tiles of 32 BT features x 32 BT envs, 4 waves of
-// BT/2 x BT/2 MFMA tiles.  Two 16-input steps of operand blocks (a block is 1
-// KB of consecutive bytes, in memory as in LDS, and a fragment read its 16
-// bytes per lane: no bank conflicts) are staged at a time, two LDS buffers, the
-// loads NS stages ahead in as many sets of registers.  The leading products
-// and the smaller ones have accumulators of their own, added at the end, so
-// that the full-size sums are rounded once per 16 inputs.
-// S15, 4096 envs, layers 226-1024 and 1024-512: 21.6 and 33.5 us (fp32 MFMA
-// kernels on 64 x 64 tiles 29.5 and 45.7; bound by the LDS reads, 24 KB per 24
-// MFMAs); with the reads ahead of the products instead of between them 23 and
-// 37; operands straight from the L2 on 64 x 128 tiles, the waves splitting the
-// inputs, 25 and 32 but no faster at 16384 envs.
+// The same on many envs, fp32: tiles of 32 BT features x 32 BT envs, 2 BT waves
+// of BT/2 x 1 MFMA tiles, each of which brings in one of the 2 BT operand tiles.
+// Two 16-input steps of operand blocks (a block is 1 KB of consecutive bytes, in
+// memory as in LDS, and a fragment read its 16 bytes per lane: no bank
+// conflicts) are staged at a time, two LDS buffers, the loads NS stages ahead in
+// as many sets of registers.
+// S15, 4096 envs, layers 226-1024 and 1024-512: 20.3 and 34.3 us (fp32 MFMA
+// kernels on 64 x 64 tiles 29.5 and 45.7; six plane products, one accumulator
+// for the smaller ones, 19.8 and 31.7); at 16384 envs 83 and 126 us, the matrix
+// cores busy for 41 and 82 of them.  With four waves on the 128 x 128 tile the
+// accumulators leave no registers for the operands (700 bytes of spills).  With
+// six products, the reads ahead of the products instead of between them took 10%
+// longer; operands straight from the L2 on 64 x 128 tiles, the waves splitting the
+// inputs, were no faster at 16384 envs.
 template <int BT>
-__global__ __launch_bounds__(256, (BT == 2 ? 2 : 1)) void layer_kernel(LayerPair p)
+__global__ __launch_bounds__(128 * BT, (BT == 2 ? 2 : 1)) void layer_kernel(LayerPair p)
 {
-    constexpr int P = 3, TM = BT / 2, TN = BT / 2, BL = 2 * BT * 2 * P;  // blocks per stage
-    constexpr int PW = BL / 4;                                                  // by wave
+    using Prod = PlaneProducts<3>;
+    constexpr int P = 3, TM = BT / 2, TN = 1, BL = 2 * BT * 2 * P;  // blocks per stage
+    constexpr int PW = 2 * P;                 // by wave: those of one of the 2 BT tiles
     constexpr int NS = BT == 4 ? 2 : 4;       // register sets: stages in flight
-    static_assert(BL % 4 == 0, "blocks by wave");
     __shared__ __attribute__((aligned(16))) uint16_t lds[2][BL * 512];
     int id = xcd_order(blockIdx.x, gridDim.x);
     const bool second = id >= p.blocks0;
@@ -339,29 +395,24 @@ __global__ __launch_bounds__(256, (BT == 2 ? 2 : 1)) void layer_kernel(LayerPair
     const int mblocks = a.M / (32 * BT);
     const int mt0 = (id % mblocks) * BT;
     const int64_t nt0 = (int64_t)(id / mblocks) * BT;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave & 1, wn = wave >> 1;
     const int nk = a.K16 / 2;       // stages
-    // this wave's blocks of a stage: consecutive ones of the tiles' 2 P each
-    const uint16_t *src[PW];
-#pragma unroll
-    for (int c = 0; c < PW; ++c) {
-        const int b = wave * PW + c, t = b / (2 * P), o = b % (2 * P);
-        src[c] = (t < BT ? a.w + (int64_t)(mt0 + t) * a.K16 * P * 512
-                          : a.x + (nt0 + t - BT) * a.K16 * P * 512) + o * 512;
-    }
+    // this wave's blocks of a stage: the consecutive ones of one tile
+    const uint16_t *src = (wave < BT ? a.w + (int64_t)(mt0 + wave) * a.K16 * P * 512
+                                     : a.x + (nt0 + wave - BT) * a.K16 * P * 512) + 8 * lane;
     u32x4_t rs[NS][PW];
     auto load = [&](int kt, u32x4_t (&r)[PW]) {
         const int k = kt < nk ? kt : nk - 1;
 #pragma unroll
-        for (int c = 0; c < PW; ++c) r[c] = *((const u32x4_t *)(src[c] + (int64_t)k * 2 * P * 512) + lane);
+        for (int c = 0; c < PW; ++c) r[c] = *(const u32x4_t *)(src + ((int64_t)k * PW + c) * 512);
     };
     auto store = [&](int buf, const u32x4_t (&r)[PW]) {
 #pragma unroll
         for (int c = 0; c < PW; ++c) *((u32x4_t *)(lds[buf] + (wave * PW + c) * 512) + lane) = r[c];
     };
-    f32x16_t acc[2][TM][TN];
+    f32x16_t acc[Prod::NG][TM][TN];
 #pragma unroll
-    for (int l = 0; l < 2; ++l)
+    for (int l = 0; l < Prod::NG; ++l)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -384,18 +435,16 @@ __global__ __launch_bounds__(256, (BT == 2 ? 2 : 1)) void layer_kernel(LayerPair
     };
     auto mma = [&](const Frags &f) {
 #pragma unroll
-        for (int d = P - 1; d >= 0; --d)
+        for (int c = 0; c < Prod::N; ++c)
 #pragma unroll
-            for (int pw = d; pw >= 0; --pw)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        f32x16_t &c = acc[d > 0][i][j];
-                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[i][pw], f.x[j][d - pw], c, 0, 0, 0);
-                    }
+                for (int j = 0; j < TN; ++j) {
+                    f32x16_t &t = acc[Prod::W[c] + Prod::X[c]][i][j];
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[i][Prod::W[c]], f.x[j][Prod::X[c]], t, 0, 0, 0);
+                }
     };
-    constexpr int NM = TM * TN * 6, NR = (TM + TN) * P;
+    constexpr int NM = TM * TN * Prod::N, NR = (TM + TN) * P;
     // stage kt in buffer kt & 1, the next one on its way in r: its second step
     // is read before the products of the first; the next stage is written
     // (its buffer was last read before the previous barrier), and its first
@@ -442,7 +491,12 @@ __global__ __launch_bounds__(256, (BT == 2 ? 2 : 1)) void layer_kernel(LayerPair
             if (nt * 32 >= a.N) continue;
             float v[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = acc[0][i][j][q] + acc[1][i][j][q];
+            for (int q = 0; q < 16; ++q) {
+                float t[Prod::NG];
+#pragma unroll
+                for (int d = 0; d < Prod::NG; ++d) t[d] = acc[d][i][j][q];
+                v[q] = join_sums<Prod::NG>(t);
+            }
             finish_tile<P>(a, mt, nt, lane, bias, v, (f32x4_t(*)[64])(lds[0] + wave * 2048));
         }
     }
@@ -478,8 +532,9 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
             for (int i = 0; i < 4; ++i) {
                 float lo = __uint_as_float(q[0][i] << 16), hi = __uint_as_float(q[0][i] & 0xFFFF0000u);
                 if constexpr (P == 3) {
-                    lo = (lo + __uint_as_float(q[1][i] << 16)) + __uint_as_float(q[2][i] << 16);
-                    hi = (hi + __uint_as_float(q[1][i] & 0xFFFF0000u)) + __uint_as_float(q[2][i] & 0xFFFF0000u);
+                    lo = join_planes(lo, __uint_as_float(q[1][i] << 16), __uint_as_float(q[2][i] << 16));
+                    hi = join_planes(hi, __uint_as_float(q[1][i] & 0xFFFF0000u),
+                                     __uint_as_float(q[2][i] & 0xFFFF0000u));
                 }
                 acc += w[2 * i] * lo;
                 acc += w[2 * i + 1] * hi;
@@ -504,22 +559,24 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
         bv = g.bias[tid];
     }
     if (tid >= 256 && tid < 256 + nv) senv[tid - 256] = g.env_n[n0 + tid - 256];
-    f32x16_t acc[TM][1];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[i][0][q] = 0.0f;
+    // (an fp32 wave takes its tiles one after the other: the accumulators of
+    // several at once would not fit beside the operands in flight)
+    constexpr int TW = P == 3 ? 1 : TM;
     const int ksl = wave % KS, mt0 = wave / KS * TM;
-    layer_mma<P, TM, 1, (P == 1 ? 4 : (TM == 3 ? 1 : 2))>(a, mt0, blockIdx.x, ksl * a.K16 / KS,
-                                                          (ksl + 1) * a.K16 / KS, lane, acc);
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int t = 0; t < TM; t += TW) {
+        f32x16_t acc[TW];
+        layer_mma<P, TW, (P == 1 ? 4 : 2)>(a, mt0 + t, blockIdx.x, ksl * a.K16 / KS, (ksl + 1) * a.K16 / KS,
+                                           lane, acc);
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            const int unit = (8 * (mt0 + i) + 2 * grp + h) ^ (r & 7);
-            *(f32x4_t *)(lds + (ksl * 32 + r) * MP + 4 * unit) =
-                f32x4_t{acc[i][0][4 * grp], acc[i][0][4 * grp + 1], acc[i][0][4 * grp + 2], acc[i][0][4 * grp + 3]};
-        }
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int grp = 0; grp < 4; ++grp) {
+                const int unit = (8 * (mt0 + t + i) + 2 * grp + h) ^ (r & 7);
+                *(f32x4_t *)(lds + (ksl * 32 + r) * MP + 4 * unit) =
+                    f32x4_t{acc[i][4 * grp], acc[i][4 * grp + 1], acc[i][4 * grp + 2], acc[i][4 * grp + 3]};
+            }
+    }
     if (tid < 128) {
         sig[tid] = expf(ls);
         sbias[tid] = bv;
@@ -545,13 +602,14 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
 // ---------------------------------------------------------------------------
 // Tile of a hidden layer of M features and 16 K16 inputs on N envs (fp32; a
 // bf16 network comes here with few envs only).  128 x 128 where that gives
-// every CU a block; else layer_small_kernel while its rounds of blocks, about
-// 8 us each, cost less than the 5 + 0.18 K16 us of one block of 64 x 64; else
-// 64 x 64.  Measured (us; small / 64 x 64 / 128 x 128), 1024 features of 256
-// inputs: 256 envs 9.2 / 7.9 / 14.9, 1000 envs 27 / 9.3 / 15, 3000 envs 73 /
-// 18.0 / 18.6, 4096 envs 96 / 23.5 / 21.6; 512 features of 1024 inputs: 512
-// envs 9.4 / 16.7 / 36, 1000 envs 16.8 / 17.4 / 37, 2048 envs 31 / 19.4 / 38,
-// 4096 envs 59 / 33.5 / 46, 8192 envs 114 / 65.6 / 56.3.
+// every CU a block; else layer_small_kernel while 2.3 us and its rounds of
+// blocks, 2 + 0.08 K16 us each, cost less than the 5.2 + 0.18 K16 us of one block
+// of 64 x 64; else 64 x 64.  Measured (us; small / 64 x 64 / 128 x 128), 1024
+// features of 256 inputs: 256 envs 5.9 / 8.1 / 14.3, 512 envs 8.9 / 8.5 / 15.1,
+// 1000 envs 15.6 / 10.3 / 15.1, 3000 envs 40 / 19.0 / 18.8, 4096 envs 52 / 23.7 /
+// 20.3; 512 features of 1024 inputs: 512 envs 9.3 / 17.4 / 38, 1000 envs 16.4 /
+// 18.4 / 39, 2048 envs 30 / 20.5 / 41, 4096 envs 57 / 34.3 / 45, 8192 envs 111 /
+// 64.6 / 54.6.
 enum { LAYER_SMALL = 0, LAYER_64, LAYER_128 };
 static int layer_tile(const LayerNet &a, int planes, int n_cu)
 {
@@ -559,7 +617,7 @@ static int layer_tile(const LayerNet &a, int planes, int n_cu)
     const int64_t cu = n_cu > 0 ? n_cu : 1;
     if (a.M % 128 == 0 && (a.M / 128) * ((a.N + 127) / 128) >= cu) return LAYER_128;
     const int64_t rounds = ((int64_t)(a.M / 32) * ((a.N + 31) / 32) + cu - 1) / cu;
-    return 800 * rounds <= 500 + 18 * a.K16 ? LAYER_SMALL : LAYER_64;
+    return 230 + rounds * (200 + 8 * a.K16) <= 520 + 18 * a.K16 ? LAYER_SMALL : LAYER_64;
 }
 
 static hipError_t launch_layer_t(int planes, LayerPair p, int tile, hipStream_t s)
@@ -572,9 +630,9 @@ static hipError_t launch_layer_t(int planes, LayerPair p, int tile, hipStream_t 
     p.blocks0 = (int)blocks[0];
     const dim3 grid((unsigned)(blocks[0] + blocks[1]));
     if (planes == 1) hipLaunchKernelGGL((layer_small_kernel<1, 8>), grid, dim3(512), 0, s, p);
-    else if (tile == LAYER_128) hipLaunchKernelGGL(layer_kernel<4>, grid, dim3(256), 0, s, p);
+    else if (tile == LAYER_128) hipLaunchKernelGGL(layer_kernel<4>, grid, dim3(512), 0, s, p);
     else if (tile == LAYER_64) hipLaunchKernelGGL(layer_kernel<2>, grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((layer_small_kernel<3, 4>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((layer_small_kernel<3, 2>), grid, dim3(512), 0, s, p);
     return hipGetLastError();
 }
 

@@ -78,10 +78,56 @@ def test_fp32_layers(actor, critic, N, pad):
     for net, got in ((d["policy"], mean), (d["critic"], value[:, None])):
         ref, bound = _bounded(net, obs[:, :N].T)
         assert (np.abs(got - ref) <= bound).all(), float((np.abs(got - ref) / bound).max())
+        # that bound holds for any signs of the errors; over a batch they cancel:
+        # fp32 sums in order are 5e-7 to 7e-7 off by norm, planes that lose
+        # their third (or a product above 2^-16 of the leading one) 6e-6; by the
+        # outputs' size over other observations, one env's may be near zero
+        typical = _bounded(net, _obs(500, 500, 9)[0].T)[0]
+        err = np.sqrt(np.mean((got - ref) ** 2) / np.mean(typical ** 2))
+        print("relative error by norm %.2e" % err, flush=True)
+        assert err <= 1e-6
     _, oa, olp = oracle.policy(d["policy"], d["config"]["seed"], obs[:, :N], env_n[:N].view(np.uint32))
     err = np.linalg.norm(action - oa, axis=1) / np.linalg.norm(oa, axis=1)
     assert (err <= 1e-4).all(), float(err.max())
     assert (np.abs(logp - olp) <= 1e-5 * np.abs(olp) + 1e-4).all()
+    ctx.close()
+
+
+# Rows of one weight: an output is one product, which fp32 rounds once (2^-24);
+# the plane product left out is below 2^-32 of it (2^-30 where an operand is
+# subnormal: its leading plane then has fewer bits) and the joining of the sums
+# rounds at 2^-8 of its size, 2^-29 allowed for both.  Weights, observations and
+# hidden activations through the whole range of fp32, subnormals with it.
+@pytest.mark.parametrize("sw,sx,s2", [(1, 1, 1), (1e-36, 1, 1), (1, 1e-36, 1), (1e-36, 1, 1e30), (1e-39, 1e10, 1),
+                                      (1e10, 1e-39, 1), (1.7e38, 0.25, 1), (1e-30, 1.7e38, 1)])
+@pytest.mark.parametrize("N,H", [(64, 256), (1000, 1024), (4100, 1024)])
+def test_fp32_single_products(N, H, sw, sx, s2):
+    print("fp32 single products N %d H %d: %g %g %g" % (N, H, sw, sx, s2), flush=True)
+    rng = np.random.default_rng(N + H)
+    d = _world([226, H, 512, 128], [226, H, 1], False)
+
+    def rows(n, k, v):
+        W = np.zeros((n, k), np.float32)
+        W[np.arange(n), np.arange(n) % k] = v
+        return W
+
+    w = ((1.0 + rng.random(H)) * sw).astype(np.float32)
+    one = rows(1, H, 1.0)
+    one[0, 0], one[0, 41] = 0.0, 1.0
+    d["policy"]["W"] = [rows(H, 226, w), rows(512, H, 1.0), rows(128, 512, np.float32(s2))]
+    d["critic"]["W"] = [rows(H, 226, w), one]
+    for net in (d["policy"], d["critic"]):
+        net["b"] = [np.zeros_like(b) for b in net["b"]]
+    obs = ((1.0 + rng.random((226, N))) * sx).astype(np.float32)
+    ctx = binding.Context(d, max_envs=N)
+    mean, _, _, value = _run(ctx, obs, np.zeros(N, np.int32), N, 128)
+    h = obs.T[:, :128].astype(np.float64) * w[:128].astype(np.float64)
+    u = U * (1.0 + 2.0 ** -5)
+    assert (np.abs(value - h[:, 41]) <= u * h[:, 41]).all()
+    ref, rel = h * float(np.float32(s2)), u if s2 == 1 else 2 * u
+    worst = float((np.abs(mean - ref) / ref).max())
+    print("worst relative error %.3e" % worst, flush=True)
+    assert worst <= rel
     ctx.close()
 
 
