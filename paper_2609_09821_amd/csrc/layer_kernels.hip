@@ -15,9 +15,9 @@
 // six products without scales 2.1e-7 to 2.3e-7); outputs of a single product at
 // most 2^-24 off (with six, 1e-7; 1e-4 and more for operands below 1e-36).
 // Eight v_mfma_f32_32x32x16_bf16 take 256 cycles where the eight
-// v_mfma_f32_32x32x2_f32 of the same 16 k take 512.  A result that is not finite
-// is formed again with fp32 multiply-adds from the operands (slow_dot), so that
-// infinities, NaNs and overflows come out as in fp32.
+// v_mfma_f32_32x32x2_f32 of the same 16 k take 512.  A sum that is not finite
+// is formed again with fp32 products (fix_sums), so that infinities, NaNs and
+// overflows come out as in fp32.
 //
 // Layout: activations and weights in 1 KB blocks, one per (tile of 32 envs or
 // output features, 16 inputs, plane): lane l = 32 h + r holds inputs 16 s +
@@ -105,25 +105,52 @@ __device__ __forceinline__ float join_sums(const float (&a)[NG])
     return s;
 }
 
-// Value (row, k) of an operand in fragment order.
-template <int P>
-__device__ __forceinline__ float plane_value(const uint16_t *x, int K16, int64_t row, int k)
+// Sums v (lane: env l & 31, register 4 grp + q: feature 8 grp + 4 (l >> 5) + q)
+// of tile (mt, nt) over the 16-input steps k0 .. k1-1 that are not finite, again
+// with fp32 products (v_mfma_f32_32x32x2_f32 on the planes' values), as one pass of
+// the whole tile: a wave pays 0.3 us per 16 inputs however many of its sums are
+// affected.  The others keep their value, so that a row does not depend on the
+// rows beside it.  S15, 64 / 4096 envs, 23 / 67 us a call: 30 / 120 us with an
+// infinity in one env's observation, 30 / 137 with one in every env's (each sum by
+// one lane, term by term: 3.6 to 9 ms).
+__device__ __forceinline__ void fix_sums(const LayerNet &a, int mt, int64_t nt, int k0, int k1, int lane,
+                                         f32x16_t &v)
 {
-    const uint16_t *q = x + (((row >> 5) * K16 + (k >> 4)) * P) * 512 + ((((k >> 3) & 1) << 5) + (row & 31)) * 8 + (k & 7);
-    const float v = bf16_to_f32(q[0]);
-    if constexpr (P == 3) return join_planes(v, bf16_to_f32(q[512]), bf16_to_f32(q[1024]));
-    return v;
-}
-
-// One output by fp32 multiply-adds.
-template <int P>
-__device__ __forceinline__ float slow_dot(const LayerNet &a, int m, int64_t n)
-{
-    float s = 0.0f;
+    bool bad = false;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) bad = bad || !(fabsf(v[q]) <= FP32_MAX);
+    if (!__any(bad)) return;
+    struct Step {
+        u32x4_t w[3], x[3];
+    };
+    auto load = [&](int s, Step &t) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            t.w[p] = *((const u32x4_t *)(a.w + (((int64_t)mt * a.K16 + s) * 3 + p) * 512) + lane);
+            t.x[p] = *((const u32x4_t *)(a.x + ((nt * a.K16 + s) * 3 + p) * 512) + lane);
+        }
+    };
+    auto value = [](const u32x4_t (&t)[3], int i) {
+        float f[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[p] = __uint_as_float(i & 1 ? t[p][i >> 1] & 0xFFFF0000u : t[p][i >> 1] << 16);
+        return join_planes(f[0], f[1], f[2]);
+    };
+    f32x16_t c;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) c[q] = 0.0f;
+    Step cur, nxt;
+    load(k0, nxt);      // (k0 < k1: the sums of no inputs are zero)
 #pragma unroll 1
-    for (int k = 0; k < 16 * a.K16; ++k)
-        s = fmaf(plane_value<P>(a.w, a.K16, m, k), plane_value<P>(a.x, a.K16, n, k), s);
-    return s;
+    for (int s = k0; s < k1; ++s) {
+        cur = nxt;
+        load(s + 1 < k1 ? s + 1 : s, nxt);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)     // inputs 16 s + i of the lower half wave, 16 s + 8 + i of the upper
+            c = __builtin_amdgcn_mfma_f32_32x32x2f32(value(cur.w, i), value(cur.x, i), c, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = fabsf(v[q]) <= FP32_MAX ? v[q] : c[q];
 }
 
 // The observation [D][ld] (env fastest) into operand blocks, a wavefront per
@@ -246,31 +273,12 @@ __device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt
         }
 }
 
-// The sums v of tile (mt, nt) (lane: env l & 31, register 4 grp + q: feature
-// 8 grp + 4 (l >> 5) + q of the tile) to the layer's output: sums that are not
-// finite formed again, bias, ReLU, planes.  fix: 1 KB of LDS per register
-// group of this wave's own.
+// The sums v of tile (mt, nt) (layout: fix_sums) to the layer's output: bias,
+// ReLU, planes.
 template <int P>
 __device__ __forceinline__ void finish_tile(const LayerNet &a, int mt, int64_t nt, int lane,
-                                            const float4 (&bias)[4], float (&v)[16], f32x4_t (*fix)[64])
+                                            const float4 (&bias)[4], float (&v)[16])
 {
-    const int h = lane >> 5, r = lane & 31;
-    if constexpr (P == 3) {
-        const int64_t n = nt * 32 + r;
-        bool bad = false;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) bad = bad || !(fabsf(v[q]) <= FP32_MAX);
-        if (__any(bad && n < a.N)) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) fix[q >> 2][lane][q & 3] = v[q];
-#pragma unroll 1
-            for (int q = 0; q < 16; ++q)
-                if (n < a.N && !(fabsf(fix[q >> 2][lane][q & 3]) <= FP32_MAX))
-                    fix[q >> 2][lane][q & 3] = slow_dot<P>(a, 32 * mt + 8 * (q >> 2) + 4 * h + (q & 3), n);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = fix[q >> 2][lane][q & 3];
-        }
-    }
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp) {
         v[4 * grp] += bias[grp].x;
@@ -322,7 +330,9 @@ __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
     for (int grp = 0; grp < 4; ++grp)
         bias[grp] = *(const float4 *)(a.bias + 32 * mt + 8 * grp + 4 * (lane >> 5));
     f32x16_t acc[1];
-    layer_mma<P, 1, U>(a, mt, nt, wave * a.K16 / WK, (wave + 1) * a.K16 / WK, lane, acc);
+    const int k0 = wave * a.K16 / WK, k1 = (wave + 1) * a.K16 / WK;
+    layer_mma<P, 1, U>(a, mt, nt, k0, k1, lane, acc);
+    if constexpr (P == 3) fix_sums(a, mt, nt, k0, k1, lane, acc[0]);
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
         red[wave][grp][lane] =
@@ -338,7 +348,7 @@ __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[4 * grp + q] = s[q];
     }
-    finish_tile<P>(a, mt, nt, lane, bias, v, red[0]);
+    finish_tile<P>(a, mt, nt, lane, bias, v);
 }
 
 // Order of a phase of the next kernel: its NM products with its NR fragment
@@ -477,7 +487,6 @@ __global__ __launch_bounds__(128 * BT, (BT == 2 ? 2 : 1)) void layer_kernel(Laye
             if ((kt += 2) >= nk) break;
         }
     }
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int mt = mt0 + wm * TM + i;
@@ -489,15 +498,19 @@ __global__ __launch_bounds__(128 * BT, (BT == 2 ? 2 : 1)) void layer_kernel(Laye
         for (int j = 0; j < TN; ++j) {
             const int64_t nt = nt0 + wn * TN + j;
             if (nt * 32 >= a.N) continue;
-            float v[16];
+            f32x16_t sum;
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 float t[Prod::NG];
 #pragma unroll
                 for (int d = 0; d < Prod::NG; ++d) t[d] = acc[d][i][j][q];
-                v[q] = join_sums<Prod::NG>(t);
+                sum[q] = join_sums<Prod::NG>(t);
             }
-            finish_tile<P>(a, mt, nt, lane, bias, v, (f32x4_t(*)[64])(lds[0] + wave * 2048));
+            fix_sums(a, mt, nt, 0, a.K16, lane, sum);
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = sum[q];
+            finish_tile<P>(a, mt, nt, lane, bias, v);
         }
     }
 }
@@ -566,8 +579,9 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
 #pragma unroll
     for (int t = 0; t < TM; t += TW) {
         f32x16_t acc[TW];
-        layer_mma<P, TW, (P == 1 ? 4 : 2)>(a, mt0 + t, blockIdx.x, ksl * a.K16 / KS, (ksl + 1) * a.K16 / KS,
-                                           lane, acc);
+        const int k0 = ksl * a.K16 / KS, k1 = (ksl + 1) * a.K16 / KS;
+        layer_mma<P, TW, (P == 1 ? 4 : 2)>(a, mt0 + t, blockIdx.x, k0, k1, lane, acc);
+        if constexpr (P == 3) fix_sums(a, mt0 + t, blockIdx.x, k0, k1, lane, acc[0]);
 #pragma unroll
         for (int i = 0; i < TW; ++i)
 #pragma unroll
@@ -590,11 +604,7 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
         if (tid == 0) slp0 = c;
     }
     __syncthreads();
-    sample_rows<512, 32, MP, KS>(g, lds, sig, sbias, slp0, senv, n0, nv, tid, [&](float mu, int e, int m) {
-        if constexpr (P == 3)
-            if (!(fabsf(mu) <= FP32_MAX)) mu = slow_dot<P>(a, m, n0 + e) + sbias[m];
-        return mu;
-    });
+    sample_rows<512, 32, MP, KS>(g, lds, sig, sbias, slp0, senv, n0, nv, tid);
 }
 
 // ---------------------------------------------------------------------------

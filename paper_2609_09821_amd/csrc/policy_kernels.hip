@@ -1201,8 +1201,7 @@ __device__ __forceinline__ void fused_last(const FusedMlpArgs &f, uint8_t *act, 
         senv[lane] = en;
     }
     __syncthreads();
-    sample_rows<512, FUSED_BN, MP, KS>(g, part, sig, sbias, slp0, senv, n0, nv, tid,
-                                       [](float mu, int, int) { return mu; });
+    sample_rows<512, FUSED_BN, MP, KS>(g, part, sig, sbias, slp0, senv, n0, nv, tid);
 }
 
 // The critic's output: v = head . h + bias over the last hidden layer's

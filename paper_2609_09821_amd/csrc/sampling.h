@@ -41,16 +41,15 @@ __device__ __forceinline__ void copy_rows_out(float *dst, const float *so, int64
 
 // Sampling of NE envs from partial tiles part [KS][NE][MP] (16-byte units
 // XOR-swizzled by env % 8): each of NTHR threads takes one (env, block of four
-// actions) at a time.  mean = bias + the partials in slice order, passed
-// through fix(mean, env, action); the noise comes from Philox; action = mean +
-// sigma z; each env's logp adds its blocks' sums in block order.  Mean and
-// action rows [NE][A] and the per-block sums [NE][33] follow the partials in
-// LDS.  All threads call it; sig, sbias, slp0 and senv are in LDS.
-template <int NTHR, int NE, int MP, int KS, class Fix>
+// actions) at a time.  mean = bias + the partials in slice order; the noise
+// comes from Philox; action = mean + sigma z; each env's logp adds its blocks'
+// sums in block order.  Mean and action rows [NE][A] and the per-block sums
+// [NE][33] follow the partials in LDS.  All threads call it; sig, sbias, slp0
+// and senv are in LDS.
+template <int NTHR, int NE, int MP, int KS>
 __device__ __forceinline__ void sample_rows(const GemmArgs &g, float *part, const float *sig,
                                             const float *sbias, const float &slp0,
-                                            const uint32_t *senv, int64_t n0, int64_t nv, int tid,
-                                            Fix fix)
+                                            const uint32_t *senv, int64_t n0, int64_t nv, int tid)
 {
     const int A = g.A;
     float *smean = part + KS * NE * MP;
@@ -76,7 +75,6 @@ __device__ __forceinline__ void sample_rows(const GemmArgs &g, float *part, cons
         for (int q = 0; q < 4; ++q) {
             const int m = 4 * j + q;
             if (m < A) {
-                mu[q] = fix(mu[q], e, m);
                 smean[e * A + m] = mu[q];
                 sact[e * A + m] = mu[q] + sig[m] * z[q];
                 lp += 0.5f * z[q] * z[q];

@@ -152,12 +152,13 @@ def test_act_value_equals_the_two_calls(bf16, N):
     ctx.close()
 
 
-@pytest.mark.parametrize("N", [40, 200, 4100])
-def test_fp32_values_that_are_not_finite(N):
+# (4100 envs: 64 x 64 tiles for 256 features, 128 x 128 for 1024)
+@pytest.mark.parametrize("N,H", [(40, 256), (200, 256), (4100, 256), (4100, 1024), (70, 1024)])
+def test_fp32_values_that_are_not_finite(N, H):
     """Infinities, NaNs and values above bf16's range in the observation and an
     infinite weight: what fp32 arithmetic gives (a NaN is cleared by the ReLU)."""
-    print("fp32 not finite N %d" % N, flush=True)
-    d = _world([226, 256, 512, 28], [226, 256, 1], False)
+    print("fp32 not finite N %d H %d" % (N, H), flush=True)
+    d = _world([226, H, 512, 28], [226, H, 1], False)
     d["policy"]["W"][1][5, 7] = np.inf
     obs, env_n = _obs(N, N)
     obs[3, 1], obs[200, 2], obs[17, 5], obs[225, 9], obs[0, N - 1] = np.inf, -np.inf, np.nan, 3.4e38, -3.4e38
@@ -178,6 +179,38 @@ def test_fp32_values_that_are_not_finite(N):
         fin = np.isfinite(x)
         scale = np.abs(np.where(fin, x, 0.0)).max(axis=1, keepdims=True) + np.zeros_like(x)
         assert (np.abs(got[fin] - x[fin]) <= 1e-4 * np.maximum(scale[fin], 1.0)).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("N,every", [(64, False), (64, True), (1000, False), (4096, False), (4096, True)])
+def test_fp32_values_that_are_not_finite_cost_little(N, every):
+    """One pass of fp32 products over the affected tiles, not a walk through each
+    sum: at most three times the call's time (measured 1.3 to 2.1), also where
+    every env holds an infinity."""
+    print("fp32 not finite, cost, N %d every env %s" % (N, every), flush=True)
+    d = _world([226, 1024, 512, 28], [226, 256, 1], False)
+    ctx = binding.Context(d, max_envs=N)
+    obs, env_n = _obs(N, N)
+    bad = obs.copy()
+    bad[7, :: 1 if every else N] = np.inf
+    f = dict(device="cuda", dtype=torch.float32)
+    out = [torch.empty((N, 28), **f), torch.empty((N, 28), **f), torch.empty((N,), **f)]
+    n = torch.from_numpy(env_n).cuda()
+    us = []
+    for x in (obs, bad):
+        g = torch.from_numpy(x).cuda()
+        best = np.inf
+        for _ in range(6):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(10):
+                ctx.policy_act(g, n, N, *out)
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 100.0)
+        us.append(best)
+    print("us per call: finite %.1f, not %.1f" % tuple(us), flush=True)
+    assert us[1] <= 3.0 * us[0]
     ctx.close()
 
 
