@@ -202,34 +202,25 @@ __global__ __launch_bounds__(256) void pack_planes_kernel(const float *__restric
         *((u32x4_t *)(w + (b * 3 + p) * 512) + lane) = u32x4_t{o[p][0], o[p][1], o[p][2], o[p][3]};
 }
 
-// out[i] = W[32][k] X[32][k]^T of weight tile mt0 + i and env tile nt over the
-// 16-input steps k0 .. k1-1.  U steps of operands are loaded at a time, two such
-// sets in turn, so that one is in flight while the other is multiplied (steps
-// past the end load the last one again).
-template <int P, int TM, int U>
-__device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt, int k0, int k1,
-                                          int lane, f32x16_t (&out)[TM])
+// acc += W[32][k] X[32][k]^T of weight tile mt and env tile nt over the 16-input
+// steps k0 .. k1-1.  U steps of operands are loaded at a time, two such sets in
+// turn, so that one is in flight while the other is multiplied (steps past the
+// end of a set load the last one again).
+template <int P, int U>
+__device__ __forceinline__ void layer_mma(const LayerNet &a, int mt, int64_t nt, int k0, int k1,
+                                          int lane, f32x16_t (&acc)[PlaneProducts<P>::NG])
 {
     using Prod = PlaneProducts<P>;
     struct Set {
-        u32x4_t w[U][TM][P], x[U][P];
+        u32x4_t w[U][P], x[U][P];
     };
-    f32x16_t acc[Prod::NG][TM];
-#pragma unroll
-    for (int d = 0; d < Prod::NG; ++d)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[d][i][q] = 0.0f;
     auto load = [&](int k, Set &t) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int s = k + u < k1 ? k + u : k1 - 1;
 #pragma unroll
             for (int p = 0; p < P; ++p) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    t.w[u][i][p] = *((const u32x4_t *)(a.w + ((int64_t)((mt0 + i) * a.K16 + s) * P + p) * 512) + lane);
+                t.w[u][p] = *((const u32x4_t *)(a.w + (((int64_t)mt * a.K16 + s) * P + p) * 512) + lane);
                 t.x[u][p] = *((const u32x4_t *)(a.x + ((nt * a.K16 + s) * P + p) * 512) + lane);
             }
         }
@@ -239,53 +230,49 @@ __device__ __forceinline__ void layer_mma(const LayerNet &a, int mt0, int64_t nt
         for (int u = 0; u < U; ++u) {
             if (k + u >= k1) break;
 #pragma unroll
-            for (int c = 0; c < Prod::N; ++c)
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    f32x16_t &t16 = acc[Prod::W[c] + Prod::X[c]][i];
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8_t, t.w[u][i][Prod::W[c]]),
-                        __builtin_bit_cast(bf16x8_t, t.x[u][Prod::X[c]]), t16, 0, 0, 0);
-                }
+            for (int c = 0; c < Prod::N; ++c) {
+                f32x16_t &t16 = acc[Prod::W[c] + Prod::X[c]];
+                t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8_t, t.w[u][Prod::W[c]]),
+                    __builtin_bit_cast(bf16x8_t, t.x[u][Prod::X[c]]), t16, 0, 0, 0);
+            }
         }
     };
     // (scheduling barriers keep the loads ahead of the products)
-    if (k0 < k1) {
-        Set ta, tb;
-        load(k0, ta);
-        for (int k = k0; k < k1; k += 2 * U) {
-            if (k + U < k1) load(k + U, tb);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(k, ta);
-            if (k + 2 * U < k1) load(k + 2 * U, ta);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(k + U, tb);
-        }
+    if (k0 >= k1) return;
+    Set ta, tb;
+    load(k0, ta);
+    for (int k = k0; k < k1; k += 2 * U) {
+        if (k + U < k1) load(k + U, tb);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(k, ta);
+        if (k + 2 * U < k1) load(k + 2 * U, ta);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(k + U, tb);
     }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            float t[Prod::NG];
-#pragma unroll
-            for (int d = 0; d < Prod::NG; ++d) t[d] = acc[d][i][q];
-            out[i][q] = join_sums<Prod::NG>(t);
-        }
 }
 
-// The sums v of tile (mt, nt) (layout: fix_sums) to the layer's output: bias,
-// ReLU, planes.
-template <int P>
-__device__ __forceinline__ void finish_tile(const LayerNet &a, int mt, int64_t nt, int lane,
-                                            const float4 (&bias)[4], float (&v)[16])
+// The fp32 sums of a tile over the steps k0 .. k1-1.
+template <int U>
+__device__ __forceinline__ f32x16_t plane_sums(const LayerNet &a, int mt, int64_t nt, int k0, int k1, int lane)
 {
+    f32x16_t acc[4], v;
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) {
-        v[4 * grp] += bias[grp].x;
-        v[4 * grp + 1] += bias[grp].y;
-        v[4 * grp + 2] += bias[grp].z;
-        v[4 * grp + 3] += bias[grp].w;
-    }
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[d][q] = 0.0f;
+    layer_mma<3, U>(a, mt, nt, k0, k1, lane, acc);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = join_sums<4>({acc[0][q], acc[1][q], acc[2][q], acc[3][q]});
+    fix_sums(a, mt, nt, k0, k1, lane, v);
+    return v;
+}
+
+// The sums v of tile (mt, nt) (layout: fix_sums), bias added, to the layer's
+// output: ReLU, planes.
+template <int P>
+__device__ __forceinline__ void finish_tile(const LayerNet &a, int mt, int64_t nt, int lane, float (&v)[16])
+{
     if constexpr (P == 3)
 #pragma unroll
         for (int q = 0; q < 16; ++q) v[q] = fmaxf(v[q], 0.0f);
@@ -309,10 +296,10 @@ __device__ __forceinline__ void finish_tile(const LayerNet &a, int mt, int64_t n
     }
 }
 
-// Hidden layer, y = ReLU(W x + b), on few envs: a block is one tile of 32
+// Hidden layer, y = ReLU(W x + b), fp32, on few envs: a block is one tile of 32
 // features x 32 envs, its 8 waves split the inputs; no operand is staged, the
 // partial tiles meet in LDS and the first wave adds them in wave order.
-template <int P, int U>
+template <int U>
 __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
 {
     constexpr int WK = 8;
@@ -329,14 +316,10 @@ __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
         bias[grp] = *(const float4 *)(a.bias + 32 * mt + 8 * grp + 4 * (lane >> 5));
-    f32x16_t acc[1];
-    const int k0 = wave * a.K16 / WK, k1 = (wave + 1) * a.K16 / WK;
-    layer_mma<P, 1, U>(a, mt, nt, k0, k1, lane, acc);
-    if constexpr (P == 3) fix_sums(a, mt, nt, k0, k1, lane, acc[0]);
+    const f32x16_t part = plane_sums<U>(a, mt, nt, wave * a.K16 / WK, (wave + 1) * a.K16 / WK, lane);
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
-        red[wave][grp][lane] =
-            f32x4_t{acc[0][4 * grp], acc[0][4 * grp + 1], acc[0][4 * grp + 2], acc[0][4 * grp + 3]};
+        red[wave][grp][lane] = f32x4_t{part[4 * grp], part[4 * grp + 1], part[4 * grp + 2], part[4 * grp + 3]};
     __syncthreads();
     if (wave > 0) return;
     float v[16];
@@ -345,10 +328,41 @@ __global__ __launch_bounds__(512, 1) void layer_small_kernel(LayerPair p)
         f32x4_t s = red[0][grp][lane];
 #pragma unroll
         for (int k = 1; k < WK; ++k) s += red[k][grp][lane];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[4 * grp + q] = s[q];
+        v[4 * grp] = s[0] + bias[grp].x;
+        v[4 * grp + 1] = s[1] + bias[grp].y;
+        v[4 * grp + 2] = s[2] + bias[grp].z;
+        v[4 * grp + 3] = s[3] + bias[grp].w;
     }
-    finish_tile<P>(a, mt, nt, lane, bias, v);
+    finish_tile<3>(a, mt, nt, lane, v);
+}
+
+// The same in bf16, a wave (and block) per tile: the sums start at the bias and
+// take the inputs in order, as in the one-launch kernel, whose bits these are;
+// a row's result does not depend on the batch it comes in.  16 steps of operands
+// (32 KB) in flight at a time, two such sets.
+__global__ __launch_bounds__(64, 1) void layer_small_bf16_kernel(LayerPair p)
+{
+    int id = xcd_order(blockIdx.x, gridDim.x);
+    const bool second = id >= p.blocks0;
+    if (second) id -= p.blocks0;
+    const LayerNet a = second ? p.a[1] : p.a[0];
+    const int lane = threadIdx.x;
+    const int mt = id % (a.M / 32);
+    const int64_t nt = id / (a.M / 32);
+    f32x16_t acc[1];
+#pragma unroll
+    for (int grp = 0; grp < 4; ++grp) {
+        const float4 b = *(const float4 *)(a.bias + 32 * mt + 8 * grp + 4 * (lane >> 5));
+        acc[0][4 * grp] = b.x;
+        acc[0][4 * grp + 1] = b.y;
+        acc[0][4 * grp + 2] = b.z;
+        acc[0][4 * grp + 3] = b.w;
+    }
+    layer_mma<1, 16>(a, mt, nt, 0, a.K16, lane, acc);
+    float v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = acc[0][q];
+    finish_tile<1>(a, mt, nt, lane, v);
 }
 
 // Order of a phase of the next kernel: its NM products with its NR fragment
@@ -509,22 +523,31 @@ __global__ __launch_bounds__(128 * BT, (BT == 2 ? 2 : 1)) void layer_kernel(Laye
             fix_sums(a, mt, nt, 0, a.K16, lane, sum);
             float v[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = sum[q];
-            finish_tile<P>(a, mt, nt, lane, bias, v);
+            for (int grp = 0; grp < 4; ++grp) {
+                v[4 * grp] = sum[4 * grp] + bias[grp].x;
+                v[4 * grp + 1] = sum[4 * grp + 1] + bias[grp].y;
+                v[4 * grp + 2] = sum[4 * grp + 2] + bias[grp].z;
+                v[4 * grp + 3] = sum[4 * grp + 3] + bias[grp].w;
+            }
+            finish_tile<P>(a, mt, nt, lane, v);
         }
     }
 }
 
 // Last layers: blocks below nb_policy sample the actions of 32 envs each (the
-// layer's 32 MT padded actions, 8 waves splitting the inputs), the rest form
-// the values of 32 envs each (the fp32 head on the planes' sum, 8 waves
-// splitting the inputs, partials added in wave order).
+// layer's 32 MT padded actions, the waves splitting the inputs), the rest form
+// the values of 32 envs each (the fp32 head on the planes' values, 8 waves
+// splitting the inputs, partials added in wave order).  bf16: the slices and the
+// order of the sums are those of the one-launch kernel, bit for bit.
 template <int P, int MT>
 __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs g, LayerHead v, int nb_policy)
 {
-    // 8 waves: KS slices of the inputs by 8 / KS groups of TM action tiles (four
-    // tiles by eight slices would not fit in LDS)
-    constexpr int MP = 32 * MT, WK = 8, KS = MT == 4 ? 4 : 8, TM = MT * KS / 8;
+    // KS slices of the inputs by MT action tiles.  fp32: 8 waves, a wave takes
+    // TM tiles, one after the other (the accumulators of several at once would
+    // not fit beside the operands in flight; four tiles by eight slices would not
+    // fit in LDS).  bf16: one tile a wave, 6 or 4 waves at three and four tiles.
+    constexpr int MP = 32 * MT, WK = 8, KS = P == 3 ? (MT == 4 ? 4 : 8) : (MT == 4 ? 1 : (MT == 3 ? 2 : 8 / MT));
+    constexpr int TM = P == 3 ? MT * KS / 8 : 1;
     __shared__ __attribute__((aligned(16))) float lds[(KS + 2) * 32 * MP + 32 * 33];
     __shared__ float sig[128], sbias[128], slp0;
     __shared__ uint32_t senv[32];
@@ -533,24 +556,45 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
     const int h = lane >> 5, r = lane & 31;
     if ((int)blockIdx.x >= nb_policy) {
         const int64_t nt = (int)blockIdx.x - nb_policy, n = nt * 32 + r;
+        if constexpr (P == 1) {
+            // a wave's inputs in order, chunks of 8 (both half waves alike)
+            const int per = v.K16 / 4;
+            float acc = 0.0f;
+#pragma unroll 4
+            for (int c = wave * per; c < (wave + 1) * per; ++c) {
+                const u32x4_t x = *((const u32x4_t *)(v.x + (nt * v.K16 + (c >> 1)) * 512) + 32 * (c & 1) + r);
+                const float *w = v.head + 8 * c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc += w[2 * i] * __uint_as_float(x[i] << 16);
+                    acc += w[2 * i + 1] * __uint_as_float(x[i] & 0xFFFF0000u);
+                }
+            }
+            if (h == 0) lds[wave * 32 + r] = acc;
+            __syncthreads();
+            if (tid < 32 && n < v.N) {
+                float s = v.head[16 * v.K16];
+#pragma unroll
+                for (int k = 0; k < WK; ++k) s += lds[k * 32 + tid];
+                v.value[n] = s;
+            }
+            return;
+        }
         float acc = 0.0f;
 #pragma unroll 2
         for (int s = wave * v.K16 / WK; s < (wave + 1) * v.K16 / WK; ++s) {
-            const u32x4_t *x = (const u32x4_t *)(v.x + ((nt * v.K16 + s) * P) * 512) + lane;
+            const u32x4_t *x = (const u32x4_t *)(v.x + ((nt * v.K16 + s) * 3) * 512) + lane;
             const float *w = v.head + 16 * s + 8 * h;
-            u32x4_t q[P];
+            u32x4_t q[3];
 #pragma unroll
-            for (int p = 0; p < P; ++p) q[p] = x[64 * p];
+            for (int p = 0; p < 3; ++p) q[p] = x[64 * p];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float lo = __uint_as_float(q[0][i] << 16), hi = __uint_as_float(q[0][i] & 0xFFFF0000u);
-                if constexpr (P == 3) {
-                    lo = join_planes(lo, __uint_as_float(q[1][i] << 16), __uint_as_float(q[2][i] << 16));
-                    hi = join_planes(hi, __uint_as_float(q[1][i] & 0xFFFF0000u),
-                                     __uint_as_float(q[2][i] & 0xFFFF0000u));
-                }
-                acc += w[2 * i] * lo;
-                acc += w[2 * i + 1] * hi;
+                acc += w[2 * i] * join_planes(__uint_as_float(q[0][i] << 16), __uint_as_float(q[1][i] << 16),
+                                              __uint_as_float(q[2][i] << 16));
+                acc += w[2 * i + 1] * join_planes(__uint_as_float(q[0][i] & 0xFFFF0000u),
+                                                  __uint_as_float(q[1][i] & 0xFFFF0000u),
+                                                  __uint_as_float(q[2][i] & 0xFFFF0000u));
             }
         }
         lds[(2 * wave + h) * 32 + r] = acc;
@@ -572,24 +616,28 @@ __global__ __launch_bounds__(512, 1) void layer_out_kernel(LayerNet a, GemmArgs 
         bv = g.bias[tid];
     }
     if (tid >= 256 && tid < 256 + nv) senv[tid - 256] = g.env_n[n0 + tid - 256];
-    // (an fp32 wave takes its tiles one after the other: the accumulators of
-    // several at once would not fit beside the operands in flight)
-    constexpr int TW = P == 3 ? 1 : TM;
-    const int ksl = wave % KS, mt0 = wave / KS * TM;
+    const int ksl = P == 3 ? wave % KS : wave / MT, mt0 = P == 3 ? wave / KS * TM : wave % MT;
+    if (P == 3 || wave < MT * KS) {
 #pragma unroll
-    for (int t = 0; t < TM; t += TW) {
-        f32x16_t acc[TW];
-        const int k0 = ksl * a.K16 / KS, k1 = (ksl + 1) * a.K16 / KS;
-        layer_mma<P, TW, (P == 1 ? 4 : 2)>(a, mt0 + t, blockIdx.x, k0, k1, lane, acc);
-        if constexpr (P == 3) fix_sums(a, mt0 + t, blockIdx.x, k0, k1, lane, acc[0]);
+        for (int t = 0; t < TM; ++t) {
+            f32x16_t v16;
+            if constexpr (P == 3) {
+                v16 = plane_sums<2>(a, mt0 + t, blockIdx.x, ksl * a.K16 / KS, (ksl + 1) * a.K16 / KS, lane);
+            } else {
+                f32x16_t acc[1];
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+                for (int q = 0; q < 16; ++q) acc[0][q] = 0.0f;
+                const int nks = a.K16 / 4;      // slices of whole K steps of 64
+                layer_mma<1, 8>(a, mt0, blockIdx.x, 4 * (ksl * nks / KS), 4 * ((ksl + 1) * nks / KS), lane, acc);
+                v16 = acc[0];
+            }
 #pragma unroll
             for (int grp = 0; grp < 4; ++grp) {
-                const int unit = (8 * (mt0 + t + i) + 2 * grp + h) ^ (r & 7);
+                const int unit = (8 * (mt0 + t) + 2 * grp + h) ^ (r & 7);
                 *(f32x4_t *)(lds + (ksl * 32 + r) * MP + 4 * unit) =
-                    f32x4_t{acc[i][4 * grp], acc[i][4 * grp + 1], acc[i][4 * grp + 2], acc[i][4 * grp + 3]};
+                    f32x4_t{v16[4 * grp], v16[4 * grp + 1], v16[4 * grp + 2], v16[4 * grp + 3]};
             }
+        }
     }
     if (tid < 128) {
         sig[tid] = expf(ls);
@@ -639,10 +687,10 @@ static hipError_t launch_layer_t(int planes, LayerPair p, int tile, hipStream_t 
     if (blocks[0] + blocks[1] > 0x7FFFFFFF) return hipErrorInvalidValue;
     p.blocks0 = (int)blocks[0];
     const dim3 grid((unsigned)(blocks[0] + blocks[1]));
-    if (planes == 1) hipLaunchKernelGGL((layer_small_kernel<1, 8>), grid, dim3(512), 0, s, p);
+    if (planes == 1) hipLaunchKernelGGL(layer_small_bf16_kernel, grid, dim3(64), 0, s, p);
     else if (tile == LAYER_128) hipLaunchKernelGGL(layer_kernel<4>, grid, dim3(512), 0, s, p);
     else if (tile == LAYER_64) hipLaunchKernelGGL(layer_kernel<2>, grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((layer_small_kernel<3, 2>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL(layer_small_kernel<2>, grid, dim3(512), 0, s, p);
     return hipGetLastError();
 }
 

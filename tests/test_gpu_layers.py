@@ -152,6 +152,29 @@ def test_act_value_equals_the_two_calls(bf16, N):
     ctx.close()
 
 
+# one to four action tiles, one to four MFMA tiles per wave of the one-launch
+# kernel, unlike depths; batches at the edges of the layer kernels' env tiles
+@pytest.mark.parametrize("actor,critic", [
+    ([226, 1024, 512, 28], [226, 1024, 1024, 512, 1]),
+    ([226, 768, 40], [226, 256, 1]),
+    ([226, 256, 1024, 70], [226, 512, 1]),
+    ([226, 512, 300, 256, 128], [226, 768, 130, 1])])
+def test_bf16_rows_do_not_depend_on_the_batch(actor, critic):
+    """A bf16 row's outputs are the same bits on the layer kernels (up to 512
+    envs) as in the one-launch kernel (more)."""
+    A = actor[-1]
+    ctx = binding.Context(_world(actor, critic, True), max_envs=1000)
+    obs, env_n = _obs(1000, 1000)
+    ref = _run(ctx, obs, env_n, 1000, A)
+    for N in (1, 32, 33, 130, 512):
+        print("bf16 rows %s %s N %d" % (actor, critic, N), flush=True)
+        for value in (True, False):
+            got = _run(ctx, obs, env_n, N, A, value)
+            for name, x, y in zip(("mean", "action", "logp", "value"), got, ref):
+                assert np.array_equal(x, y[:N]), name
+    ctx.close()
+
+
 # (4100 envs: 64 x 64 tiles for 256 features, 128 x 128 for 1024)
 @pytest.mark.parametrize("N,H", [(40, 256), (200, 256), (4100, 256), (4100, 1024), (70, 1024)])
 def test_fp32_values_that_are_not_finite(N, H):
