@@ -104,8 +104,8 @@ bool fused_policy_fits(const im_ctx *c)
     return true;
 }
 
-// Networks that the layer kernels hold (fp32: every one with a hidden layer;
-// bf16: those of the one-launch kernel), and up to how many envs they run there.
+// Networks that the layer kernels hold: fp32 ones with a hidden layer, bf16 ones
+// of the one-launch kernel.
 bool layered_policy(const im_ctx *c) { return c->L >= 2 && (!c->d_wp.empty() || !c->d_wf.empty()); }
 bool layered_critic(const im_ctx *c)
 {
@@ -115,6 +115,22 @@ int64_t layered_most(const im_ctx *c)
 {
     return c->dtype == IM_DTYPE_BF16 ? im::LAYER_BF16_MAX : INT64_MAX;
 }
+// Whether a call on n_envs runs the policy and / or the critic there (a bf16
+// network gives the same bits either way).
+bool run_layered(const im_ctx *c, int64_t n_envs, bool policy, bool critic)
+{
+    if ((policy && !layered_policy(c)) || (critic && !layered_critic(c))) return false;
+    if (c->dtype != IM_DTYPE_BF16) return true;
+    auto worth = [](const std::vector<int> &M_pad, const std::vector<int> &K_pad, int layers, int hidden) {
+        int64_t bytes = 0;
+        for (int l = 0; l < layers; ++l) bytes += 2ll * M_pad[l] * K_pad[l];
+        return bytes >= im::LAYER_BF16_BYTES * hidden;
+    };
+    return n_envs <= im::LAYER_BF16_MAX && ((policy && worth(c->M_pad, c->K_pad, c->L, c->L - 1)) ||
+                                            (critic && worth(c->critic.M_pad, c->critic.K_pad, c->critic.L - 1,
+                                                             c->critic.L - 1)));
+}
+
 // Envs whose hidden activations pass through a workspace: a network that the
 // one-launch kernel holds (one_launch) leaves its larger batches to that.
 int64_t ws_envs(const im_ctx *c, bool one_launch)
@@ -1069,7 +1085,7 @@ im_status policy_layers(im_ctx *c, const float *obs, int64_t ld_obs, const uint3
 {
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     const uint64_t esz = bf16 ? 2 : 4;
-    if (layered_policy(c) && n_envs <= layered_most(c))
+    if (run_layered(c, n_envs, true, false))
         return layered(c, obs, ld_obs, env_n, n_envs, mean, action, logp, nullptr, stream);
     if (bf16 && !c->d_wf.empty()) {
         const FusedMlpArgs f = policy_fused_args(c, obs, ld_obs, env_n, n_envs, mean, action, logp);
@@ -1334,7 +1350,7 @@ im_status value_layers(im_ctx *c, const float *obs, int64_t ld_obs, int64_t n_en
     const auto &cr = c->critic;
     const bool bf16 = c->dtype == IM_DTYPE_BF16;
     hipError_t e;
-    if (layered_critic(c) && n_envs <= layered_most(c))
+    if (run_layered(c, n_envs, false, true))
         return layered(c, obs, ld_obs, nullptr, n_envs, nullptr, nullptr, nullptr, value, st);
     if (!cr.d_wf.empty()) {
         const FusedMlpArgs f = value_fused_args(c, obs, ld_obs, n_envs, value);
@@ -1380,7 +1396,7 @@ im_status im_policy_act_value(im_ctx *c, const float *obs, int64_t ld_obs, const
     if ((s = check_act_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     if ((s = check_value_sizes(c, ld_obs, n_envs)) != IM_OK) return s;
     const hipStream_t st = (hipStream_t)stream;
-    if (layered_policy(c) && layered_critic(c) && n_envs <= std::min(layered_most(c), im::LAYER_PAIR_MAX))
+    if (n_envs <= im::LAYER_PAIR_MAX && run_layered(c, n_envs, true, true))
         return layered(c, obs, ld_obs, env_n, n_envs, mean, action, logp, value, st);
     if (!c->d_wf.empty() && !c->critic.d_wf.empty()) {
         const hipError_t e = launch_policy_value_fused(

@@ -119,12 +119,21 @@ hipError_t launch_layers(int planes, const LayerNet *a, int n, int n_cu, hipStre
 // The policy's sampled layer (a, g) and / or the critic's head (v); null: none.
 hipError_t launch_layer_out(int planes, const LayerNet *a, const GemmArgs *g, const LayerHead *v, hipStream_t s);
 
-// Batches of a bf16 network up to this many envs run layer by layer on
-// launch_layers, which spreads a layer's weights over the chip: the one-launch
-// kernel's few blocks each stream all of them (us, S24 policy / with critic, in
-// layers and in one launch: 64 envs 23 / 23 and 51 / 51, 512 envs 30 / 41 and
-// 52 / 52, 1024 envs 41 / 63 and 52 / 52; S15 1024 envs 26 / 40 and 24 / 26).
-constexpr int64_t LAYER_BF16_MAX = 512;
+// Batches of a bf16 network up to LAYER_BF16_MAX envs run layer by layer on
+// launch_layers, which spreads a layer's weights over the chip, where the weights
+// are at least LAYER_BF16_BYTES per hidden layer: the one-launch kernel's few
+// blocks each stream all of them (7.6 us and 11 us per MB), the layers cost their
+// launches (3.6 us each from the host, 2.5 to 4 in a graph).  Policy alone / with a
+// critic like it, in layers and in one launch, us: S24 64 envs 24.1 / 24.0 and
+// 47.6 / 101.8 (in two launches; one for both is 50), 512 envs 26.7 / 29.6 and 52 /
+// 51, 1000 envs 30.3 / 39.2 and 52 / 51, 1500 envs 37.5 / 50.5 and 51 / 50; S15
+// 1000 envs 18.8 / 22.6 and 24.0 / 24.0, 1500 envs 21.1 / 28.5 and 24 / 24: past
+// 1024 the call with a critic is no faster.  226-1024-28 (576 KB per hidden layer)
+// 14.8 / 15.0 and 14.0 / 14.3 from the host, 9.9 and 13.7 in a graph; 226-512-512-28
+// (410 KB) 18.1 / 18.5 and 16.5 / 16.7; 226-256-256-256-256-28 (188 KB) 25 / 25 and
+// 15 / 15.
+constexpr int64_t LAYER_BF16_MAX = 1024;
+constexpr int64_t LAYER_BF16_BYTES = 1 << 19;
 // Batches up to this many envs run the policy's and the critic's layers in
 // shared launches (above, each fills the chip alone).
 constexpr int64_t LAYER_PAIR_MAX = 8192;

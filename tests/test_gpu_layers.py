@@ -1,4 +1,4 @@
-"""GPU tests of the layer kernels (fp32 networks as three bf16 planes, bf16
+"""GPU tests of the layer kernels (fp32 networks as three bf16 planes, larger bf16
 networks on few envs): batches at the edges of their tiles and of the rules
 that choose them, odd widths, networks of unlike depth, and values that are
 not finite.
@@ -133,7 +133,7 @@ def test_fp32_single_products(N, H, sw, sx, s2):
 
 # both sides of the batch sizes where a network changes kernels, and where the
 # two networks stop sharing launches
-@pytest.mark.parametrize("bf16,N", [(True, 1), (True, 512), (True, 513), (False, 500), (False, 8192),
+@pytest.mark.parametrize("bf16,N", [(True, 1), (True, 512), (True, 513), (True, 1024), (True, 1025), (False, 500), (False, 8192),
                                     (False, 8193)])
 def test_act_value_equals_the_two_calls(bf16, N):
     print("act_value bf16 %s N %d" % (bf16, N), flush=True)
@@ -153,20 +153,21 @@ def test_act_value_equals_the_two_calls(bf16, N):
 
 
 # one to four action tiles, one to four MFMA tiles per wave of the one-launch
-# kernel, unlike depths; batches at the edges of the layer kernels' env tiles
+# kernel, unlike depths (the small critics run in it alone, on the layer kernels
+# beside their policy); batches at the edges of the layer kernels' env tiles
 @pytest.mark.parametrize("actor,critic", [
     ([226, 1024, 512, 28], [226, 1024, 1024, 512, 1]),
-    ([226, 768, 40], [226, 256, 1]),
-    ([226, 256, 1024, 70], [226, 512, 1]),
-    ([226, 512, 300, 256, 128], [226, 768, 130, 1])])
+    ([226, 1024, 40], [226, 256, 1]),
+    ([226, 512, 1024, 70], [226, 512, 1]),
+    ([226, 1024, 700, 600, 128], [226, 768, 900, 1])])
 def test_bf16_rows_do_not_depend_on_the_batch(actor, critic):
-    """A bf16 row's outputs are the same bits on the layer kernels (up to 512
+    """A bf16 row's outputs are the same bits on the layer kernels (up to 1024
     envs) as in the one-launch kernel (more)."""
     A = actor[-1]
-    ctx = binding.Context(_world(actor, critic, True), max_envs=1000)
-    obs, env_n = _obs(1000, 1000)
-    ref = _run(ctx, obs, env_n, 1000, A)
-    for N in (1, 32, 33, 130, 512):
+    ctx = binding.Context(_world(actor, critic, True), max_envs=1100)
+    obs, env_n = _obs(1100, 1100)
+    ref = _run(ctx, obs, env_n, 1100, A)
+    for N in (1, 32, 33, 130, 1024):
         print("bf16 rows %s %s N %d" % (actor, critic, N), flush=True)
         for value in (True, False):
             got = _run(ctx, obs, env_n, N, A, value)
@@ -257,12 +258,12 @@ def test_policy_graph_outlives_a_wider_critic(bf16):
     has been handed out since."""
     N, A = 64, 28
     print("policy graph, then a wider critic, bf16 %s" % bf16, flush=True)
-    d = _world([226, 256, 256, A], [226, 256, 1], bf16)
+    d = _world([226, 1024, 256, A], [226, 256, 1], bf16)
     ctx = binding.Context(d, max_envs=N)
     obs, env_n = _obs(N, N)
     graph, g, out = _captured(ctx, obs, env_n, N, A)
     eager = [o.clone() for o in out]
-    wide = binding.Description(_world([226, 256, 256, A], [226, 1024, 1024, 1], bf16))
+    wide = binding.Description(_world([226, 1024, 256, A], [226, 2048, 2048, 1], bf16))
     binding.im_set_critic(ctx.ptr, wide.critic)
     filled = [torch.full((n,), 3.0, device="cuda") for n in [1 << 14] * 64 + [1 << 20] * 32]
     for _ in range(3):
@@ -284,7 +285,7 @@ def test_policy_survives_a_critic_that_does_not_fit():
     GiB) is refused; the policy's calls go on as before."""
     N, A = 64, 28
     print("critic that does not fit", flush=True)
-    d = _world([226, 256, A], [226, 16384, 1], True)
+    d = _world([226, 1024, A], [226, 16384, 1], True)
     ctx = binding.Context(d, max_envs=1 << 24, critic=False)
     obs, env_n = _obs(N, N)
     graph, g, out = _captured(ctx, obs, env_n, N, A)
