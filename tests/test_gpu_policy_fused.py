@@ -6,11 +6,14 @@ Cases cover the widths and depths the kernel takes: hidden layers of 256,
 512, 768 and 1024 features (one to four MFMA tiles per wave), 32 to 128
 padded actions, one layer (no hidden layer) up to eight, an observation 961
 wide (1024 padded: the widest LDS row), a single env, ragged last blocks of
-64 envs and a full grid of 16384 envs.  Policies it does not hold (a
+64 envs and a full grid of 16384 envs.  Networks of at least 512 KB per hidden
+layer run on the layer kernels up to 1024 envs: their cases come with more envs
+too, where the one-launch kernel takes them.  Policies it does not hold (a
 1280-wide hidden layer, nine layers) take the per-layer kernels, checked the
 same way.  The critic variant (hidden layers, then the fp32 value head)
-runs over the same widths and depths.  Tolerances as in the full-size parity
-test.
+runs over the same widths and depths, and both in one launch on either side of
+8192 envs, where its blocks no longer all fit the chip at once.  Tolerances as
+in the full-size parity test.
 """
 import numpy as np
 import pytest
@@ -79,8 +82,11 @@ def check_policy(d, N):
     (COMB64, [1024], 69, 333),            # 1024-wide padded observation, three action tiles
     (CHAIN6, [512], 96, 777),             # three full action tiles
     (CHAIN6, [256], 128, 300),            # the widest action set: four full tiles
+    (CHAIN6, [512, 1024], 40, 1025),      # (beyond the layer kernels' batches)
+    (COMB64, [1024], 69, 1101),
+    (CHAIN6, [1024, 1024], 128, 1153),
 ], ids=["256-768", "1024-512-full-grid", "one-env", "one-layer", "eight-layers", "obs-961",
-        "96-actions", "128-actions"])
+        "96-actions", "128-actions", "512-1024-more", "obs-961-more", "128-actions-1024-more"])
 def test_fused_policy_shapes(parent, hidden, A, N):
     check_policy(_world(parent, hidden, A, 5), N)
 
@@ -119,6 +125,35 @@ def check_value(d, N):
     (CHAIN6, [256] * 8, 130),             # eight hidden layers
     (COMB64, [1024, 256], 333),           # 1024-wide padded observation
     (CHAIN6, [1280], 700),                # too wide: per-layer kernels
-], ids=["256-768", "1024-512-full-grid", "one-env", "eight-hidden", "obs-961", "hidden-1280"])
+    (COMB64, [1024, 256], 1101),          # (beyond the layer kernels' batches)
+], ids=["256-768", "1024-512-full-grid", "one-env", "eight-hidden", "obs-961", "hidden-1280",
+        "obs-961-more"])
 def test_fused_critic_shapes(parent, hidden, N):
     check_value(_world(parent, [256], 8, 9, critic_hidden=hidden), N)
+
+
+@pytest.mark.parametrize("N", [1101, 8257])
+@pytest.mark.parametrize("parent,hidden,A,critic_hidden", [
+    (CHAIN6, [256] * 7, 8, [256] * 8),            # eight layers each
+    (COMB64, [1024], 69, [1024, 256]),            # the widest observation
+    (CHAIN6, [512], 128, [768]),                  # four full action tiles
+], ids=["eight-layers", "obs-961", "128-actions"])
+def test_fused_policy_and_critic_shapes(parent, hidden, A, critic_hidden, N):
+    """Both in one launch: the bits of the two calls, which are checked against
+    the oracle."""
+    d = _world(parent, hidden, A, 11, critic_hidden=critic_hidden)
+    check_policy(d, N)
+    check_value(d, N)
+    D = d["policy"]["dims"][0]
+    ctx = binding.Context(d, max_envs=N)
+    f = dict(device="cuda", dtype=torch.float32)
+    obs = torch.randn((D, N), generator=torch.Generator("cuda").manual_seed(N), **f)
+    n = torch.arange(N, dtype=torch.int32, device="cuda")
+    one, two = ([torch.empty((N, A), **f), torch.empty((N, A), **f), torch.empty(N, **f), torch.empty(N, **f)]
+                for _ in range(2))
+    ctx.policy_act_value(obs, n, N, *one)
+    ctx.policy_act(obs, n, N, *two[:3])
+    ctx.value(obs, N, two[3])
+    torch.cuda.synchronize()
+    ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(one, two))
