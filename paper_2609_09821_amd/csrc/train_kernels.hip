@@ -11,9 +11,11 @@
 //   forward  Y^T  = W   X^T          (out x Mb)
 //   backward dX^T = W^T dZ^T         (in x Mb, masked by the ReLU)
 //   weights  dW   = dZ^T X           (out x in, reduced over the minibatch)
-// run on one GEMM kernel C[m][n] = sum_k A[m][k] B(k, n): A always has k
-// contiguous (weights, transposed weights, dZ^T), B either k-major [k][n]
-// (activations, gradients) or n-major [n][k] (X^T for the weight gradient).
+// are C[m][n] = sum_k A[m][k] B(k, n): A always has k contiguous (weights,
+// transposed weights, dZ^T), B either k-major [k][n] (activations, gradients) or
+// n-major [n][k] (X^T for the weight gradient).  The first two run on
+// fgemm_kernel where the output width is a multiple of its 256 rows, the rest on
+// tgemm_kernel.
 #include <hip/hip_runtime.h>
 
 #include "device_math.h"
@@ -28,11 +30,6 @@ typedef unsigned int u32x2_v __attribute__((ext_vector_type(2)));
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 #define IM_LDS3 __attribute__((address_space(3)))
 
-// Sum of x over each group of W (16 or 32) consecutive lanes, aligned to W,
-// returned in the group's last lane: an inclusive scan within each 16-lane
-// row (DPP row shifts by 1, 2, 4, 8; lanes shifted in from outside the row
-// read zero), then for W = 32 the total of the even row added into the odd
-// row (row broadcast of lane 15).  The order of the additions is fixed.
 // x plus the value DPP control CTRL brings in (0 where it brings none: lanes
 // outside ROW_MASK, or shifted in from outside the row).
 template <int CTRL, int ROW_MASK>
@@ -42,6 +39,11 @@ __device__ __forceinline__ float dpp_add(float x)
     return x + __builtin_bit_cast(float, t);
 }
 
+// Sum of x over each group of W (16 or 32) consecutive lanes, aligned to W,
+// returned in the group's last lane: an inclusive scan within each 16-lane
+// row (DPP row shifts by 1, 2, 4, 8; lanes shifted in from outside the row
+// read zero), then for W = 32 the total of the even row added into the odd
+// row (row broadcast of lane 15).  The order of the additions is fixed.
 template <int W>
 __device__ __forceinline__ float lane_group_sum(float x)
 {
@@ -56,21 +58,21 @@ __device__ __forceinline__ float lane_group_sum(float x)
 }
 
 // ---------------------------------------------------------------------------
-// GEMM: tiles of BM = 64 WM rows by BN columns (WM x 2 waves, each wave
-// 64 x BN/2 = 2 x BN/64 MFMA 32x32x16 tiles).  launch_tgemm picks WM = 4
-// (256 rows, 8 waves, 512 threads) when M is a multiple of 256, else WM = 2
-// (128 rows, 4 waves), and BN = 256 when N is a multiple of 256, else 128:
-// 256 x 256 tiles of 8 waves wherever the shape allows.  K step 64, two LDS
-// stages; loads of stage k+2 are in flight while stage k runs.  k-contiguous
-// operands sit in LDS rows of 72 bf16 (144 bytes: fragment reads free of bank
-// conflicts).  A k-major B tile is stored as it lies in memory, [64 k][BN n]
-// in rows of BN + 16 bf16, and its
-// MFMA fragments are read with the LDS transpose read: in every 16-lane
-// group, lane 4j+q addresses row k0+j, columns n0+4q..n0+4q+3, and lane l
-// receives rows k0..k0+3 of column n0+l (two reads give the 8 consecutive k
-// of a bf16 fragment; the 32-byte row shift of the padding keeps a group's
-// four rows on distinct banks).  A split K (weight gradients: K = the
-// minibatch) takes one block per tile and split.  All operands are zero-padded to whole tiles.
+// GEMM: tiles of BM = 64 WM rows by 256 columns (WM x 2 waves, each wave
+// 64 x 128 = 2 x 4 MFMA 32x32x16 tiles).  WM = 4 (256 rows, 8 waves, 512
+// threads) for weight gradients whose M is a multiple of 256, else WM = 2 (128
+// rows, 4 waves): the other weight gradients, the actor's output layer, and the
+// hidden layers that fgemm_kernel does not take.  K step 64, two LDS stages;
+// loads of stage k+2 are in flight while stage k runs.  k-contiguous operands
+// sit in LDS rows of 72 bf16 (144 bytes: fragment reads free of bank
+// conflicts).  A k-major B tile is stored as it lies in memory, [64 k][256 n]
+// in rows of 272 bf16, and its MFMA fragments are read with the LDS transpose
+// read: in every 16-lane group, lane 4j+q addresses row k0+j, columns n0+4q..
+// n0+4q+3, and lane l receives rows k0..k0+3 of column n0+l (two reads give the
+// 8 consecutive k of a bf16 fragment; the 32-byte row shift of the padding keeps
+// a group's four rows on distinct banks).  A split K (weight gradients: K = the
+// minibatch) takes one block per tile and split.  All operands are zero-padded
+// to whole tiles.
 // ---------------------------------------------------------------------------
 template <bool BT, int EPI, int WM>
 __global__ __launch_bounds__(128 * WM) void tgemm_kernel(TGemmPair p)
