@@ -586,37 +586,45 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 // ---------------------------------------------------------------------------
 // Critic head (width-1 output layer) on feature-major activations.
 // ---------------------------------------------------------------------------
-// Two samples per thread, a wavefront per block, each sample's sum over the
-// rows in order; rows in chunks of 32, two chunk buffers in turn so that 32 to
-// 64 loads are in flight (rows past the last load the last).  Eight samples
-// per thread with 4 loads in flight left 32768 samples on 16 blocks (50 us;
-// 524288 samples 112 us; now 24 and 125 us).
+// SPT samples per thread, a wavefront per block, each sample's sum over the rows
+// in order; rows in chunks of 64 / SPT, two chunk buffers in turn, so that one to
+// two chunks are in flight (rows past the last load the last).  Few samples want
+// two each, so that more wavefronts share them (32768 samples of 512 rows: 23 us,
+// with four 26), many want four, for longer reads (131072 samples 33 and 30 us,
+// 524288 130 and 115; eight 172).
+template <int SPT>
 __global__ __launch_bounds__(64) void head_forward_kernel(const uint16_t *__restrict__ h, int K,
                                                           int64_t Mb, const float *__restrict__ w,
                                                           const float *__restrict__ b,
                                                           float *__restrict__ v)
 {
-    constexpr int C = 32;
-    const int64_t j = ((int64_t)blockIdx.x * 64 + threadIdx.x) * 2;
-    uint32_t xa[C], xb[C];
+    constexpr int C = 64 / SPT, W = SPT / 2;
+    typedef uint32_t words_t __attribute__((ext_vector_type(W)));
+    const int64_t j = ((int64_t)blockIdx.x * 64 + threadIdx.x) * SPT;
+    words_t xa[C], xb[C];
     float wa, wb;      // the chunk's weights, one per lane
-    auto load = [&](int k0, uint32_t (&x)[C], float &wl) {
+    auto load = [&](int k0, words_t (&x)[C], float &wl) {
         const int kw = k0 + (threadIdx.x & (C - 1));
         wl = w[kw < K ? kw : K - 1];
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             const int k = k0 + i < K ? k0 + i : K - 1;
-            x[i] = *(const uint32_t *)(h + k * Mb + j);
+            x[i] = *(const words_t *)(h + k * Mb + j);
         }
     };
-    float s0 = 0.0f, s1 = 0.0f;
-    auto sum = [&](int k0, const uint32_t (&x)[C], float wl) {
+    float s[SPT];
+#pragma unroll
+    for (int q = 0; q < SPT; ++q) s[q] = 0.0f;
+    auto sum = [&](int k0, const words_t (&x)[C], float wl) {
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             if (k0 + i >= K) break;
             const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), i));
-            s0 += wk * __uint_as_float(x[i] << 16);
-            s1 += wk * __uint_as_float(x[i] & 0xFFFF0000u);
+#pragma unroll
+            for (int q = 0; q < W; ++q) {
+                s[2 * q] += wk * __uint_as_float(x[i][q] << 16);
+                s[2 * q + 1] += wk * __uint_as_float(x[i][q] & 0xFFFF0000u);
+            }
         }
     };
     load(0, xa, wa);
@@ -626,7 +634,8 @@ __global__ __launch_bounds__(64) void head_forward_kernel(const uint16_t *__rest
         load(k0 + 2 * C, xa, wa);
         if (k0 + C < K) sum(k0 + C, xb, wb);
     }
-    *(float2 *)(v + j) = make_float2(s0 + b[0], s1 + b[0]);
+#pragma unroll
+    for (int q = 0; q < SPT; q += 2) *(float2 *)(v + j + q) = make_float2(s[q] + b[0], s[q + 1] + b[0]);
 }
 
 // dZ^T[k][j] = w[k] dV[j] where h[k][j] > 0 (bf16), for the last hidden
@@ -757,7 +766,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs r)
 // its actions' partials over its lanes by a fixed pattern, the block's four
 // waves of an action in order.  One thread per sample over all actions left
 // 32768 samples on 128 blocks of 4 waves (28 actions: 43 us; 524288 samples
-// of 69 actions 216 us; now 17 and 204 us).
+// of 69 actions 224 us; now 17 and 227 us, the latter with the output layer's
+// bias sums, 17 us as a pass of their own).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void loss_kernel(LossArgs a)
 {
@@ -1050,7 +1060,10 @@ hipError_t launch_head_forward(const uint16_t *h, int K, int64_t Mb, const float
                                float *v, hipStream_t s)
 {
     // Mb is a multiple of 256
-    hipLaunchKernelGGL(head_forward_kernel, dim3((unsigned)(Mb / 128)), dim3(64), 0, s, h, K, Mb, w, b, v);
+    if (Mb >= 131072)
+        hipLaunchKernelGGL(head_forward_kernel<4>, dim3((unsigned)(Mb / 256)), dim3(64), 0, s, h, K, Mb, w, b, v);
+    else
+        hipLaunchKernelGGL(head_forward_kernel<2>, dim3((unsigned)(Mb / 128)), dim3(64), 0, s, h, K, Mb, w, b, v);
     return hipGetLastError();
 }
 

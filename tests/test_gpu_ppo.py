@@ -382,6 +382,38 @@ def test_minibatch_gradient_of_unlike_networks(actor, critic):
     ctx.close()
 
 
+# both sides of the sample count where the critic's output layer takes more
+# samples per thread; 300 rows, a remainder of either's chunks
+@pytest.mark.parametrize("N", [130816, 131392])
+def test_critic_output_by_sample_count(N):
+    print("critic output of %d samples" % N, flush=True)
+    d = synth.make_world(3, n_envs=64)
+    d["policy"] = synth.make_policy(np.random.default_rng(1), [226, 64, 28], True)
+    d["critic"] = synth.make_policy(np.random.default_rng(2), [226, 300, 1], True)
+    ctx = binding.Context(d, max_envs=N)
+    ctx.ppo_setup(N)
+    ro = binding.RolloutStorage(ctx, N, 1)
+    gen = torch.Generator("cuda").manual_seed(N)
+    for x in (ro.obs, ro.action, ro.mean, ro.logp, ro.value, ro.advantage, ro.ret):
+        x.copy_(torch.randn(x.shape, generator=gen, device="cuda"))
+    ro.summary.zero_()
+    perm = torch.arange(N // 64, dtype=torch.int32, device="cuda")[None]
+    batch = binding.ppo_batch(ro, perm, torch.full((1,), 1e-3, device="cuda"))
+    g = torch.empty(ctx.ppo_params(), device="cuda")
+    ctx.ppo_grad(batch, binding.ppo_params(**dict(binding.PPO_DEFAULTS, epochs=1, minibatches=1)), 0, 0, g)
+    h = ctx.ppo_read("critic_hidden", 0)[:300].double()
+    v = ctx.ppo_read("value")[0].double()
+    torch.cuda.synchronize()
+    w = torch.from_numpy(np.asarray(d["critic"]["W"][1][0], np.float64)).cuda()
+    b = float(d["critic"]["b"][1][0])
+    ref = (w[:, None] * h).sum(0) + b
+    bound = 302 * U32 * ((w.abs()[:, None] * h.abs()).sum(0) + abs(b)) + U32 * ref.abs()
+    assert v.shape[0] == (N + 255) // 256 * 256
+    assert bool(((v - ref).abs() <= bound).all()), float(((v - ref).abs() / bound).max())
+    assert float(ref.std()) > 0.01
+    ctx.close()
+
+
 def test_adam_step_on_the_gpu_gradient():
     # one epoch of one minibatch: the update is one norm clip + Adam step on the
     # minibatch gradient; the oracle's step on the GPU's own gradient, element
