@@ -111,9 +111,10 @@ bool layered_critic(const im_ctx *c)
 {
     return c->critic.L >= 2 && (!c->critic.d_wp.empty() || !c->critic.d_wf.empty());
 }
-int64_t layered_most(const im_ctx *c)
+// Envs that the layer kernels' buffers hold (an fp32 call on more takes parts).
+int64_t layered_envs(const im_ctx *c)
 {
-    return c->dtype == IM_DTYPE_BF16 ? im::LAYER_BF16_MAX : INT64_MAX;
+    return std::min(c->max_envs, c->dtype == IM_DTYPE_BF16 ? im::LAYER_BF16_MAX : im::LAYER_F32_PART);
 }
 // Whether a call on n_envs runs the policy and / or the critic there (a bf16
 // network gives the same bits either way).
@@ -131,11 +132,12 @@ bool run_layered(const im_ctx *c, int64_t n_envs, bool policy, bool critic)
                                                              c->critic.L - 1)));
 }
 
-// Envs whose hidden activations pass through a workspace: a network that the
-// one-launch kernel holds (one_launch) leaves its larger batches to that.
+// Envs whose hidden activations pass through a workspace at a time: a bf16
+// network that the one-launch kernel holds (one_launch) leaves its larger batches
+// to that, one beyond its widths takes a call's envs at once.
 int64_t ws_envs(const im_ctx *c, bool one_launch)
 {
-    return one_launch ? std::min(c->max_envs, im::LAYER_BF16_MAX) : c->max_envs;
+    return c->dtype == IM_DTYPE_BF16 && !one_launch ? c->max_envs : layered_envs(c);
 }
 // Buffer i of the critic's activations, alone.
 void *critic_ws(const im_ctx *c, int i) { return c->critic.d_ws[i] ? c->critic.d_ws[i] : c->d_ws[i]; }
@@ -817,7 +819,7 @@ im_status im_create(const im_config *cfg, const im_skeleton *sk, const im_clip *
             c->ws_bytes[1] = wsb;
         }
         if (layered_policy(c))
-            IM_TRY_ALLOC(c->d_xp, ws_size(c->dtype, std::min(max_envs, layered_most(c)), c->K_pad[0]));
+            IM_TRY_ALLOC(c->d_xp, ws_size(c->dtype, layered_envs(c), c->K_pad[0]));
         // large bf16 batches of the per-layer kernels stage the observation as
         // bf16 rows for the first layer (the one-launch kernel stages it in LDS)
         if (pol->dtype == IM_DTYPE_BF16 && max_envs > SMALL_BATCH && c->d_wf.empty())
@@ -1003,11 +1005,10 @@ FusedMlpArgs value_fused_args(const im_ctx *c, const float *obs, int64_t ld_obs,
 // Hidden layers, then the sampled layer and / or the critic's head on the layer
 // kernels (layer_kernels.hip): the policy (mean not null), the critic (value
 // not null) or both.  Both together, the critic's activations have buffers of
-// their own.
-im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n, int64_t n_envs,
-                  float *mean, float *action, float *logp, float *value, hipStream_t st)
+// their own.  The n_envs envs from env0 on, of arrays that start at env 0.
+im_status layered_part(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n, int64_t env0,
+                       int64_t n_envs, float *mean, float *action, float *logp, float *value, hipStream_t st)
 {
-    if (n_envs <= 0) return IM_OK;
     const auto &cr = c->critic;
     const int planes = c->dtype == IM_DTYPE_BF16 ? 1 : 3;
     struct Net {
@@ -1036,8 +1037,8 @@ im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *e
         a.N = n_envs;
         return a;
     };
-    hipError_t e = im::launch_stage_planes(planes, obs, ld_obs, c->D, n_envs, (*nets[0].K_pad)[0] / 16, c->d_xp,
-                                           st);
+    hipError_t e = im::launch_stage_planes(planes, obs + env0, ld_obs, c->D, n_envs, (*nets[0].K_pad)[0] / 16,
+                                           c->d_xp, st);
     if (e != hipSuccess) return hip_fail(e, "observation staging launch");
     for (int l = 0; l < levels; ++l) {
         LayerNet a[2];
@@ -1055,7 +1056,8 @@ im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *e
     im::LayerHead v{};
     if (mean) {
         out = layer(nets[0], c->L - 1);
-        g.N = n_envs;
+        g.env0 = env0;
+        g.N = env0 + n_envs;
         g.bias = c->d_b[c->L - 1];
         g.mean = mean;
         g.action = action;
@@ -1071,10 +1073,25 @@ im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *e
         v.head = cr.d_head;
         v.K16 = cr.K_head / 16;
         v.N = n_envs;
-        v.value = value;
+        v.value = value + env0;
     }
     e = im::launch_layer_out(planes, mean ? &out : nullptr, mean ? &g : nullptr, value ? &v : nullptr, st);
     return e == hipSuccess ? IM_OK : hip_fail(e, "output layer launch");
+}
+
+// The same on any number of envs: more than LAYER_F32_PART (fp32) in equal parts,
+// each about half of that or more, so that the tiles are those of one pass.
+im_status layered(im_ctx *c, const float *obs, int64_t ld_obs, const uint32_t *env_n, int64_t n_envs,
+                  float *mean, float *action, float *logp, float *value, hipStream_t st)
+{
+    const int64_t parts = (n_envs + im::LAYER_F32_PART - 1) / im::LAYER_F32_PART;
+    const int64_t per = parts > 0 ? round_up((n_envs + parts - 1) / parts, 128) : 1;
+    for (int64_t env0 = 0; env0 < n_envs; env0 += per) {
+        const im_status s = layered_part(c, obs, ld_obs, env_n, env0, std::min(per, n_envs - env0), mean, action,
+                                         logp, value, st);
+        if (s != IM_OK) return s;
+    }
+    return IM_OK;
 }
 
 // The policy's layers; *staged: the first layer read the observation through
@@ -1301,8 +1318,7 @@ im_status im_set_critic(im_ctx *c, const im_policy *k)
                 hipSuccess)
             return oom("observation staging");
         if (!c->d_xp && (!bf16 || !cr.d_wf.empty()) &&
-            dev_alloc(c, &c->d_xp, ws_size(c->dtype, std::min(c->max_envs, layered_most(c)), cr.K_pad[0])) !=
-                hipSuccess)
+            dev_alloc(c, &c->d_xp, ws_size(c->dtype, layered_envs(c), cr.K_pad[0])) != hipSuccess)
             return oom("observation staging");
         const int64_t most = bf16 ? LAYER_BF16_MAX : LAYER_PAIR_MAX;
         if (layered_policy(c) && (bf16 ? !cr.d_wf.empty() : true))

@@ -43,6 +43,8 @@ struct GemmArgs {
     uint32_t y_bytes;    // extent of y in bytes (set by the launcher)
     int x16_staged;      // non-zero: x16 already holds this observation (staged by an
                          // earlier layer of the same call), the staging pass is skipped
+    int64_t env0;        // layer kernels: the launch's first env; N is then the end of its envs,
+                         // and mean, action, logp and env_n start at env 0
 };
 
 // The whole bf16 policy in one launch (policy_kernels.hip): hidden widths
@@ -137,6 +139,12 @@ constexpr int64_t LAYER_BF16_BYTES = 1 << 19;
 // Batches up to this many envs run the policy's and the critic's layers in
 // shared launches (above, each fills the chip alone).
 constexpr int64_t LAYER_PAIR_MAX = 8192;
+// fp32 calls on more envs run in parts of at most this many (a multiple of 128), so
+// that the planes' workspace, 6 bytes a value, stays bounded: from 393216 envs on
+// it is below 4 bytes a value of every env.  Parts of 65536 cost 2 to 3% between
+// 70000 and 131072 envs (S15 policy and critic 1586 -> 1632 and 2900 -> 2960 us),
+// each part's last round of tiles being partly empty.
+constexpr int64_t LAYER_F32_PART = 1 << 18;
 
 // Rollout end (rollout_kernels.hip).
 struct GaeArgs {

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(512, P == 3 && MT == 1 ? 4 : 1) void layer_out_kern
         return;
     }
     const int A = g.A;
-    const int64_t n0 = (int64_t)blockIdx.x * 32;
+    const int64_t n0 = g.env0 + (int64_t)blockIdx.x * 32;
     const int64_t nv = g.N - n0 < 32 ? g.N - n0 : 32;
     float ls = 0.0f, bv = 0.0f;
     if (tid < A) {
@@ -734,7 +734,7 @@ hipError_t launch_stage_planes(int planes, const float *obs, int64_t ld, int D, 
 
 hipError_t launch_layer_out(int planes, const LayerNet *a, const GemmArgs *g, const LayerHead *v, hipStream_t s)
 {
-    const int64_t np = a ? (g->N + 31) / 32 : 0, nv = v ? (v->N + 31) / 32 : 0;
+    const int64_t np = a ? (g->N - g->env0 + 31) / 32 : 0, nv = v ? (v->N + 31) / 32 : 0;
     if (np + nv == 0) return hipSuccess;
     const int mt = a ? a->M / 32 : 1;
     if (a && (a->M % 32 || mt < 1 || mt > 4 || g->A > a->M || a->K16 <= 0)) return hipErrorInvalidValue;

@@ -131,6 +131,46 @@ def test_fp32_single_products(N, H, sw, sx, s2):
     ctx.close()
 
 
+@pytest.mark.parametrize("N", [262144, 262145, 540001])
+def test_fp32_calls_in_parts(N):
+    """More than 262144 envs run in equal parts: the same bits as the rows of a
+    call in one part, noise by the env's index in the call, nothing written past
+    the end."""
+    print("fp32 in parts N %d" % N, flush=True)
+    A, M = 5, 20000
+    d = _world([226, 40, 30, A], [226, 20, 30, 1], False)
+    ctx = binding.Context(d, max_envs=N)
+    obs, env_n = _obs(N, N + 3)
+    got = _run(ctx, obs, env_n, N, A, value=False)
+    f = dict(device="cuda", dtype=torch.float32)
+    for n0 in (0, N - M):
+        g = torch.from_numpy(np.ascontiguousarray(obs[:, n0:n0 + M])).cuda()
+        n = torch.from_numpy(env_n[n0:n0 + M].copy()).cuda()
+        out = [torch.full((M + 1, A), 7.0, **f), torch.full((M + 1, A), 7.0, **f), torch.full((M + 1,), 7.0, **f),
+               torch.full((M + 1,), 7.0, **f)]
+        ctx.policy_act(g, n, M, *out[:3])
+        ctx.value(g, M, out[3])
+        torch.cuda.synchronize()
+        assert all(bool((o[M] == 7.0).all()) for o in out)
+        rows = [o[:M].cpu().numpy() for o in out]
+        assert np.array_equal(rows[0], got[0][n0:n0 + M]) and np.array_equal(rows[3], got[3][n0:n0 + M])
+    _, oa, olp = oracle.policy(d["policy"], d["config"]["seed"], obs[:, :N], env_n[:N].view(np.uint32))
+    assert (np.linalg.norm(got[1] - oa, axis=1) <= 1e-4 * np.linalg.norm(oa, axis=1)).all()
+    assert (np.abs(got[2] - olp) <= 1e-5 * np.abs(olp) + 1e-4).all()
+    ctx.close()
+
+
+def test_fp32_workspace_of_many_envs():
+    """The planes take no more memory than the activations of all the envs would
+    as fp32 values (1024 wide, two buffers)."""
+    envs = 1 << 20
+    ctx = binding.Context(_world([226, 1024, 512, 28], [226, 1024, 512, 1], False), max_envs=envs)
+    held = binding.im_get_info(ctx.ptr).device_bytes
+    ctx.close()
+    print("device bytes %d" % held, flush=True)
+    assert held <= 2 * envs * 1024 * 4
+
+
 # both sides of the batch sizes where a network changes kernels, and where the
 # two networks stop sharing launches
 @pytest.mark.parametrize("bf16,N", [(True, 1), (True, 512), (True, 513), (True, 1024), (True, 1025), (False, 500), (False, 8192),
