@@ -31,7 +31,9 @@
  * structure-of-arrays with a leading dimension `ld` (>= n_envs): component
  * c of body b of env e is at  base[(b * NC + c) * ld + e].  A context owns
  * its device copies of the skeleton, clip and weight tables and a policy
- * workspace allocated at creation, for up to `max_envs`.
+ * workspace allocated at creation, for up to `max_envs` (fp32: for at most
+ * 262144 at a time, 6 bytes per padded unit of the observation and of two hidden
+ * layers; a critic with up to 8192 envs in the same launches has its own).
  *
  * Hot calls (im_env_step_fused, im_policy_act, im_reset_envs,
  * im_standin_physics) allocate nothing, read no device memory on the host
@@ -467,6 +469,11 @@ enum {
  * samples: float32 master weights (from the current policy and critic),
  * Adam moments, activation and gradient buffers.  Not hot: allocates and
  * synchronises.  Needs a critic; a second call resets the optimizer.
+ * Memory: 2 bytes per sample for every padded hidden unit of both networks
+ * (and an eighth of a byte for its ReLU mask), two gradient buffers of the
+ * widest layer per network, since both run level by level together, and up to
+ * 1024 partial tiles of 64 KB per network: 11 GB for two networks of 1024, 1024
+ * and 512 hidden units and 524288 samples.
  * Parameter vector order: actor W_0 [out][in], b_0, ..., log_std, critic
  * W_0, b_0, ..., the critic's output layer W [1][in], b [1].
  */

@@ -152,8 +152,9 @@ __device__ __forceinline__ int xcd_order(int b, int n)
 }
 
 // Sum over a wavefront in float64, returned in lane 63: an inclusive scan
-// within each 16-lane row (DPP row shifts by 1, 2, 4, 8), then row 0 into row 1 and row 2 into row 3 (row broadcast of lane 15), then
-// rows 0-1 into rows 2-3 (row broadcast of lane 31).
+// within each 16-lane row (DPP row shifts by 1, 2, 4, 8), then row 0 into row 1
+// and row 2 into row 3 (row broadcast of lane 15), then rows 0-1 into rows 2-3
+// (row broadcast of lane 31).
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_add(double x)
 {

@@ -275,8 +275,9 @@ struct ReduceJob {
     float *out;
     const double *part;
     int parts, prows;
-    int pairs;             // parts 2k and 2k + 1 (floats) are added in fp32 first: sums over 256
-                           // columns from products that leave them by 128
+    int pairs;             // parts 2k and 2k + 1 (floats) are added in fp32 first: fgemm_kernel's sums
+                           // over 128 columns then count as tgemm_kernel's over 256, so that a bias
+                           // gradient has the same bits on either kernel
     float *row_out;
 };
 constexpr int MAX_REDUCE = 3;

@@ -117,8 +117,8 @@ __device__ __forceinline__ void sample_epilogue(const GemmArgs &g, float *so, in
 template <int WGN, int MT>
 __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
 {
-    constexpr int KC = 32, NT = 1;
-    constexpr int BM = MT * 32, BN = WGN * NT * 32;
+    constexpr int KC = 32;
+    constexpr int BM = MT * 32, BN = WGN * 32;
     constexpr int NTHR = 64 * WGN;
     constexpr int LDA = KC + 4;                  // floats per LDS row (16-byte pad)
     constexpr int STAGE = (BM + BN) * LDA;
@@ -132,7 +132,6 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wn = wave;
     const int64_t n0 = (int64_t)blockIdx.y * BN;
     const float *W = (const float *)g.w;
     const float *X = (const float *)g.x;
@@ -147,9 +146,8 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
         (void *)W, (short)0, (int)g.w_bytes, 0x00020000);
     // three register stages: the global loads of chunk k+3 go out while chunk
     // k is multiplied and chunk k+1 (loaded two chunks earlier) is stored to LDS
-    constexpr int RB = O_CH;
-    f32x4_t ra0[A_CH], rb0[RB], ra1[A_CH], rb1[RB], ra2[A_CH], rb2[RB];
-    auto load_global = [&](int k0, f32x4_t (&ra)[A_CH], f32x4_t (&rb)[RB]) {
+    f32x4_t ra0[A_CH], rb0[O_CH], ra1[A_CH], rb1[O_CH], ra2[A_CH], rb2[O_CH];
+    auto load_global = [&](int k0, f32x4_t (&ra)[A_CH], f32x4_t (&rb)[O_CH]) {
 #pragma unroll
         for (int c = 0; c < A_CH; ++c) {
             const int v = tid + c * NTHR;
@@ -157,24 +155,22 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
             const uint32_t off = (uint32_t)((r * g.K_pad + k0 + q * 4) * 4);
             ra[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(wr, off, 0, 0));
         }
-        {
 #pragma unroll
-            for (int c = 0; c < O_CH; ++c) {
-                const int v = tid + c * NTHR;
-                const int kk = v / (BN / 4), nq = (v % (BN / 4)) * 4;
-                const uint32_t off = (uint32_t)((((int64_t)(k0 + kk)) * g.ld_x + n0 + nq) * 4);
-                if (vec_obs) {
-                    rb[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-                } else {
-                    rb[c][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off, 0, 0));
-                    rb[c][1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 4, 0, 0));
-                    rb[c][2] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 8, 0, 0));
-                    rb[c][3] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 12, 0, 0));
-                }
+        for (int c = 0; c < O_CH; ++c) {
+            const int v = tid + c * NTHR;
+            const int kk = v / (BN / 4), nq = (v % (BN / 4)) * 4;
+            const uint32_t off = (uint32_t)((((int64_t)(k0 + kk)) * g.ld_x + n0 + nq) * 4);
+            if (vec_obs) {
+                rb[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
+            } else {
+                rb[c][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off, 0, 0));
+                rb[c][1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 4, 0, 0));
+                rb[c][2] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 8, 0, 0));
+                rb[c][3] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off + 12, 0, 0));
             }
         }
     };
-    auto store_lds = [&](int buf, const f32x4_t (&ra)[A_CH], const f32x4_t (&rb)[RB]) {
+    auto store_lds = [&](int buf, const f32x4_t (&ra)[A_CH], const f32x4_t (&rb)[O_CH]) {
         float *As = lds + buf * STAGE;
         float *Bs = As + BM * LDA;
 #pragma unroll
@@ -182,26 +178,22 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
             const int v = tid + c * NTHR;
             *(f32x4_t *)(As + (v / (KC / 4)) * LDA + (v % (KC / 4)) * 4) = ra[c];
         }
-        {
 #pragma unroll
-            for (int c = 0; c < O_CH; ++c) {
-                const int v = tid + c * NTHR;
-                const int kk = v / (BN / 4), nq = (v % (BN / 4)) * 4;
-                Bs[(nq + 0) * LDA + kk] = rb[c][0];
-                Bs[(nq + 1) * LDA + kk] = rb[c][1];
-                Bs[(nq + 2) * LDA + kk] = rb[c][2];
-                Bs[(nq + 3) * LDA + kk] = rb[c][3];
-            }
+        for (int c = 0; c < O_CH; ++c) {
+            const int v = tid + c * NTHR;
+            const int kk = v / (BN / 4), nq = (v % (BN / 4)) * 4;
+            Bs[(nq + 0) * LDA + kk] = rb[c][0];
+            Bs[(nq + 1) * LDA + kk] = rb[c][1];
+            Bs[(nq + 2) * LDA + kk] = rb[c][2];
+            Bs[(nq + 3) * LDA + kk] = rb[c][3];
         }
     };
 
-    f32x16_t acc[MT][NT];
+    f32x16_t acc[MT][1];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
 
     // MFMA 4t + q of a chunk takes, in each half h = lane / 32 of the wave,
     // element q of the 16-byte run at k = 8t + 4h (operands A and B alike), so
@@ -210,22 +202,19 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
     auto compute = [&](int buf) {
         const float *As = lds + buf * STAGE;
         const float *Bs = As + BM * LDA;
-        const int arow = lane & 31, brow = wn * (NT * 32) + (lane & 31);
+        const int arow = lane & 31, brow = wave * 32 + (lane & 31);
         const int kh = 4 * (lane >> 5);
 #pragma unroll
         for (int t = 0; t < KC / 8; ++t) {
-            f32x4_t af[MT], bfr[NT];
+            f32x4_t af[MT];
 #pragma unroll
             for (int i = 0; i < MT; ++i) af[i] = *(const f32x4_t *)(As + (arow + i * 32) * LDA + 8 * t + kh);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bfr[j] = *(const f32x4_t *)(Bs + (brow + j * 32) * LDA + 8 * t + kh);
+            const f32x4_t bf = *(const f32x4_t *)(Bs + brow * LDA + 8 * t + kh);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][q], bfr[j][q], acc[i][j], 0, 0, 0);
+                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][q], bf[q], acc[i][0], 0, 0, 0);
         }
     };
 
@@ -237,8 +226,8 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
     if (nk > 2) load_global(2 * KC, ra2, rb2);
     // chunk kt: registers of chunk kt+1 in stage (kt+1) % 3, loads of kt+3 into
     // stage kt % 3 (stored to LDS in the previous iteration)
-    auto step = [&](int kt, const f32x4_t (&sa)[A_CH], const f32x4_t (&sb)[RB], f32x4_t (&la)[A_CH],
-                    f32x4_t (&lb)[RB]) {
+    auto step = [&](int kt, const f32x4_t (&sa)[A_CH], const f32x4_t (&sb)[O_CH], f32x4_t (&la)[A_CH],
+                    f32x4_t (&lb)[O_CH]) {
         compute(kt & 1);
         if (kt + 1 < nk) store_lds((kt + 1) & 1, sa, sb);
         if (kt + 3 < nk) load_global((kt + 3) * KC, la, lb);
@@ -251,7 +240,7 @@ __global__ __launch_bounds__(64 * WGN) void gemm_f32_kernel(GemmArgs g)
     }
 
     const int64_t nv = g.N - n0 < BN ? g.N - n0 : BN;
-    sample_epilogue<NTHR, MT, NT>(g, lds, n0, nv, wn * NT * 32, tid, acc);
+    sample_epilogue<NTHR, MT, 1>(g, lds, n0, nv, wave * 32, tid, acc);
 }
 
 // ---------------------------------------------------------------------------

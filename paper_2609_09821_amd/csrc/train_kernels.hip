@@ -591,7 +591,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 // two chunks are in flight (rows past the last load the last).  Few samples want
 // two each, so that more wavefronts share them (32768 samples of 512 rows: 23 us,
 // with four 26), many want four, for longer reads (131072 samples 33 and 30 us,
-// 524288 130 and 115; eight 172).
+// 524288 130 and 117; eight 172).
 template <int SPT>
 __global__ __launch_bounds__(64) void head_forward_kernel(const uint16_t *__restrict__ h, int K,
                                                           int64_t Mb, const float *__restrict__ w,
@@ -766,8 +766,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs r)
 // its actions' partials over its lanes by a fixed pattern, the block's four
 // waves of an action in order.  One thread per sample over all actions left
 // 32768 samples on 128 blocks of 4 waves (28 actions: 43 us; 524288 samples
-// of 69 actions 224 us; now 17 and 227 us, the latter with the output layer's
-// bias sums, 17 us as a pass of their own).
+// of 69 actions 222 us; now 17 and 223 us, with the output layers' bias sums,
+// 9 and 21 us as passes of their own).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void loss_kernel(LossArgs a)
 {
