@@ -24,6 +24,7 @@ using namespace im;
 namespace im {
 struct TrainState;
 void free_train(TrainState *t);
+int64_t train_bytes(const TrainState *t);   // 0: none
 }  // namespace im
 
 struct im_ctx {
@@ -855,7 +856,7 @@ im_status im_get_info(const im_ctx *c, im_info *info)
     info->policy_dtype = c->dtype;
     info->max_depth = c->max_depth;
     info->max_envs = c->max_envs;
-    info->device_bytes = c->device_bytes;
+    info->device_bytes = c->device_bytes + im::train_bytes(c->train);
     return IM_OK;
 }
 
@@ -1553,6 +1554,8 @@ void free_train(TrainState *t)
     for (void *p : t->allocs) hipFree(p);
     delete t;
 }
+
+int64_t train_bytes(const TrainState *t) { return t ? t->bytes : 0; }
 
 }  // namespace im
 

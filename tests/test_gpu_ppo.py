@@ -620,3 +620,27 @@ def test_ppo_setup_rejects_operands_of_4_gib():
     ctx.ppo_update(binding.ppo_batch(ro, perm, lr), binding.ppo_params(epochs=1, minibatches=1))
     torch.cuda.synchronize()
     ctx.close()
+
+
+def test_ppo_setup_memory():
+    """im_get_info counts the training state, and it is what the header says:
+    the hidden units and their masks, two gradient buffers per network, the
+    split sums (at most 1024 tiles and one round more), and per sample the
+    observation, the rollout's columns and the outputs."""
+    Mb, hidden = 131072, 1024 + 1024 + 512
+    d = synth.make_world(4, n_envs=128)
+    dims = [d["policy"]["W"][0].shape[1], 1024, 1024, 512]
+    A = d["policy"]["W"][-1].shape[0]
+    d["policy"] = synth.make_policy(np.random.default_rng(1), dims + [A], True)
+    d["critic"] = synth.make_policy(np.random.default_rng(2), dims + [1], True)
+    ctx = binding.Context(d, max_envs=128)
+    before = binding.im_get_info(ctx.ptr).device_bytes
+    ctx.ppo_setup(Mb)
+    grown = binding.im_get_info(ctx.ptr).device_bytes - before
+    ctx.close()
+    state = 2 * hidden * Mb * 17 // 8 + 4 * 1024 * Mb * 2
+    print("training state %d bytes, activations and gradients %d" % (grown, state), flush=True)
+    inputs = Mb * (2 * 384 + 2 * 128 + 4 * (3 * A + 8)) + 2 * 1024 * 8 * (Mb // 128 + 1) + 1024 * 8 * (Mb // 2048 + 1)
+    # per weight, padded: master, two moments, gradient (fp32), two bf16 copies
+    weights = (2 * (384 * 1024 + 1024 * 1024 + 1024 * 512) + 512 * 128) * 20
+    assert state + inputs <= grown <= state + inputs + 2 * (1024 + 64) * 65536 + weights + (4 << 20)
