@@ -57,9 +57,9 @@ SHARED_SOURCES = []
 TRAFFIC_KIB = {
     # policy: one entry per launch of im_policy_act (a bf16 policy is one launch)
     "policy": {"sources": ["policy_kernels.hip", "sampling.h", "device_math.h", "launch.h"],
-               "sha": "6f98e92e2b344db5", "workloads": {
+               "sha": "30165aa3e0e8fab9", "workloads": {
         4: {"fetch": [109680.5], "write": [35584.0]},
-        5: {"fetch": [138924.5], "write": [58368.0]}}},
+        5: {"fetch": [139097.3], "write": [58368.0]}}},
     "env": {"sources": ["env_kernels.hip", "device_math.h", "tables.h"], "sha": "f457d7902db47cc0", "workloads": {
         4: {"fetch": [61770.7], "write": [169488.8]},
         5: {"fetch": [183967.1], "write": [413743.0]}}},

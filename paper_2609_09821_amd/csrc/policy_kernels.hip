@@ -1300,7 +1300,8 @@ __global__ __launch_bounds__(512) void policy_fused_bf16_kernel(FusedMlpArgs f)
 // network's weights; in several rounds the policy's longer blocks would all
 // fall on the same CUs (S15, 16381 envs: 61.5 us against 60.5 in two
 // launches), so the policy's blocks come first.  S24 policy and critic, 4096
-// envs (64 blocks each): 96.7 -> 49.6 us; S15, 16381 envs: 56.8 -> 56.3 us.
+// envs (64 blocks each): 96.7 -> 49.7 us; S15, 16381 envs: 57.0 -> 56.5 us, which
+// is no more than runs differ.
 __global__ __launch_bounds__(512) void policy_value_fused_bf16_kernel(FusedMlpArgs fp, FusedMlpArgs fv,
                                                                       int nb, bool by_xcd)
 {
